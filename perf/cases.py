@@ -1,6 +1,6 @@
 """The work whose speed is followed, case by case.
 
-Four kinds of pass, each as a serving program makes it:
+Three kinds of pass, each as a serving program makes it:
 
 * ``layer``: one attention layer of a planned batch, the append of the step's
   new K/V rows and then the attention over them (the plan is built once per
