@@ -12,7 +12,7 @@
 //    are reduced across the LPT lanes of a token with DPP row operations, the
 //    softmax is online in the log2 domain, and every lane group keeps its own
 //    running (max, sum, output) state; the states are merged across lane
-//    groups with cross-lane shuffles and across waves through LDS. Each KV byte
+//    groups with cross-lane swaps and across waves through LDS. Each KV byte
 //    is read once for all G heads (grouped-query sharing). Arithmetic runs on
 //    the vector ALUs in fp32, except for groups of eight (or, when asked for,
 //    four) query heads (bf16 or fp8 KV, head_dim 128), whose products run on
@@ -261,6 +261,10 @@ template <> struct RowMath<KV_FP8, AUG_BF16> {
 __device__ __forceinline__ void store_partial(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void store_partial2(float* p, float a, float b) {
+  const uint64_t v = static_cast<uint64_t>(__float_as_uint(a)) | (static_cast<uint64_t>(__float_as_uint(b)) << 32);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ float load_partial(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -346,18 +350,25 @@ __device__ __forceinline__ void finish_split(const AttnArgs& a, int group, int n
 // row items (VALU)
 // ---------------------------------------------------------------------------
 
+// A wave's result of a row item in LDS: per head D unnormalised outputs, then
+// the running maximum and row sum, padded so that every row is 16-byte aligned.
+constexpr int row_lds_stride(int d) { return d + 4; }
+
 // Last step of a row item: every wave has written its unnormalised output
-// o[G][D], running maximum and row sum to lds[wave][head][D + 2]; the waves'
-// results are merged (log-sum-exp) and stored as the output rows, or as the
-// item's split-K partial.
+// o[G][D], running maximum and row sum to lds[wave][head]; the waves' results
+// are merged (log-sum-exp) and stored as the output rows, or as the item's
+// split-K partial. A thread takes up to four neighbouring dims of one head,
+// so that a group of eight heads is one pass over the workgroup with the
+// statistics read once, and partials leave in 8-byte stores.
 template <int D, int G, int OT, int NW>
 __device__ __forceinline__ void row_merge_waves(const WorkItem& it, const AttnArgs& a, float* lds) {
-  constexpr int ROW = D + 2;
+  constexpr int ROW = row_lds_stride(D);
+  constexpr int W = G * D >= 4 * 64 * NW ? 4 : 2;   // dims per thread
   const int kvh = it.kvh;
   __syncthreads();
-  for (int idx = threadIdx.x; idx < G * D; idx += 64 * NW) {
-    const int h = idx / D;
-    const int d = idx % D;
+  for (int idx = threadIdx.x; idx < G * D / W; idx += 64 * NW) {
+    const int h = idx * W / D;
+    const int d = idx * W % D;
     float mw[NW];
     float mx = kNegBig;
 #pragma unroll
@@ -365,19 +376,25 @@ __device__ __forceinline__ void row_merge_waves(const WorkItem& it, const AttnAr
       mw[w] = lds[(w * G + h) * ROW + D];
       mx = fmaxf(mx, mw[w]);
     }
-    float ls = 0.f, os = 0.f;
+    float ls = 0.f, os[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) os[k] = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
+      const float* src = lds + (w * G + h) * ROW;
       const float f = __builtin_amdgcn_exp2f(mw[w] - mx);
-      ls += lds[(w * G + h) * ROW + D + 1] * f;
-      os += lds[(w * G + h) * ROW + d] * f;
+      ls += src[D + 1] * f;
+#pragma unroll
+      for (int k = 0; k < W; ++k) os[k] += src[d + k] * f;
     }
     if (it.part < 0) {
       const int64_t off = (static_cast<int64_t>(it.q_row0) * a.hq + static_cast<int64_t>(kvh) * G + h) * D + d;
-      store_out<OT>(a.out, off, os / ls);
+#pragma unroll
+      for (int k = 0; k < W; ++k) store_out<OT>(a.out, off + k, os[k] / ls);
     } else {
       float* pp = a.partials + static_cast<int64_t>(it.part) * aug::partial_floats(G, D);
-      store_partial(pp + h * D + d, os);
+#pragma unroll
+      for (int k = 0; k < W; k += 2) store_partial2(pp + h * D + d + k, os[k], os[k + 1]);
       if (d == 0) {
         store_partial(pp + G * D + h, mx);
         store_partial(pp + G * D + G + h, ls);
@@ -385,6 +402,76 @@ __device__ __forceinline__ void row_merge_waves(const WorkItem& it, const AttnAr
     }
   }
   if (it.part >= 0) finish_split<D, G, OT, 64 * NW>(a, it.group, 1, lds);
+}
+
+// Reduction of a row item's lane groups (lanes with equal `dl`; they differ
+// in the lane bits from LPT up). v_permlane32_swap and v_permlane16_swap of
+// two heads' registers put each head's two halves side by side, so one add
+// reduces both and leaves head k in the lanes whose bit is clear and head
+// k + LIVE / 2 where it is set: each exchange halves what is left to reduce,
+// where a shuffle per value would move everything every time: 24 exchanges in
+// place of 80 LDS permutes for four heads of head_dim 128. Lane bit 3
+// (eight-lane token rows) goes through a DPP row rotation. The end of a row
+// item is latency on a small batch: an item of 480 keys streams for 13.5 us
+// and spent 1.9 us here. With the wave merge below and the scalar item loads,
+// 16 decodes of the 8B layer went from 26.5 to 25.5 us per layer with their
+// append, 64 decodes and two chunks at head_dim 64 from 33.9 to 31.5 us; large
+// batches, bound by HBM, are unchanged (298 us for 256 decodes).
+__device__ __forceinline__ float lane8_other(float v) { return dpp<0x128>(v); }   // row_ror:8 = lane ^ 8
+
+template <int MASK>
+__device__ __forceinline__ void lane_halves(float a, float b, float* x, float* y) {
+  static_assert(MASK == 16 || MASK == 32, "one swap instruction each");
+  if constexpr (MASK == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    *x = __uint_as_float(r[0]);
+    *y = __uint_as_float(r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    *x = __uint_as_float(r[0]);
+    *y = __uint_as_float(r[1]);
+  }
+}
+
+template <int MASK>
+__device__ __forceinline__ float lane_max(float v) {
+  if constexpr (MASK == 8) {
+    return fmaxf(v, lane8_other(v));
+  } else {
+    float x, y;
+    lane_halves<MASK>(v, v, &x, &y);
+    return fmaxf(x, y);
+  }
+}
+
+// One exchange over lane bit MASK of the LIVE heads still held: afterwards
+// slot k < LIVE / 2 holds head k, or k + LIVE / 2 in lanes with the bit set.
+// With one head left, and for bit 3, every lane gets the sum.
+template <int MASK, int LIVE, int N>
+__device__ __forceinline__ void lane_sum(float (*v)[N]) {
+  constexpr int HALF = LIVE / 2;
+  if constexpr (MASK == 8) {
+#pragma unroll
+    for (int k = 0; k < LIVE; ++k)
+#pragma unroll
+      for (int e = 0; e < N; ++e) v[k][e] += lane8_other(v[k][e]);
+  } else if constexpr (LIVE >= 2) {
+#pragma unroll
+    for (int k = 0; k < HALF; ++k)
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        float x, y;
+        lane_halves<MASK>(v[k][e], v[k + HALF][e], &x, &y);
+        v[k][e] = x + y;
+      }
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      float x, y;
+      lane_halves<MASK>(v[0][e], v[0][e], &x, &y);
+      v[0][e] = x + y;
+    }
+  }
 }
 
 
@@ -597,36 +684,44 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
     }
   }
 
-  // merge the TPI lane groups of this wave (lanes with equal dl)
+  // merge the TPI lane groups of this wave (lanes with equal dl): one common
+  // maximum per head, then sums over lane bits 5, 4 (and 3), halving the heads
+  // a lane still holds at each of the first two
+  float mg[G], acc[G][VEC + 1];
 #pragma unroll
-  for (int mask = LPT; mask < 64; mask <<= 1) {
+  for (int h = 0; h < G; ++h) {
+    mg[h] = m[h];
+    if constexpr (LPT <= 8) mg[h] = lane_max<8>(mg[h]);
+    if constexpr (LPT <= 16) mg[h] = lane_max<16>(mg[h]);
+    mg[h] = lane_max<32>(mg[h]);
+    const float f = __builtin_amdgcn_exp2f(m[h] - mg[h]);
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float mo = __shfl_xor(m[h], mask);
-      const float lo = __shfl_xor(l[h], mask);
-      const float mn = fmaxf(m[h], mo);
-      const float a1 = __builtin_amdgcn_exp2f(m[h] - mn);
-      const float a2 = __builtin_amdgcn_exp2f(mo - mn);
-      l[h] = l[h] * a1 + lo * a2;
+    for (int e = 0; e < VEC; ++e) acc[h][e] = o[h][e] * f;
+    acc[h][VEC] = l[h] * f;
+  }
+  constexpr int L1 = G >= 2 ? G / 2 : 1;                    // heads per lane after bit 5
+  constexpr int L2 = LPT <= 16 && L1 >= 2 ? L1 / 2 : L1;    // after bit 4
+  lane_sum<32, G>(acc);
+  if constexpr (LPT <= 16) lane_sum<16, L1>(acc);
+  if constexpr (LPT <= 8) lane_sum<8, L2>(acc);
+  const int h0 = (G >= 2 && (lane & 32) ? G / 2 : 0) + (L2 < L1 && (lane & 16) ? L1 / 2 : 0);
+  // lane bits that split no heads hold copies: one of them writes
+  const bool writes = (G >= 2 || !(lane & 32)) && (LPT > 16 || L2 < L1 || !(lane & 16)) && (LPT > 8 || !(lane & 8));
+
+  // merge the waves through LDS: [wave][head][D + 4]
+  constexpr int ROW = row_lds_stride(D);
+  if (writes) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) o[h][e] = o[h][e] * a1 + __shfl_xor(o[h][e], mask) * a2;
-      m[h] = mn;
+    for (int k = 0; k < L2; ++k) {
+      float* dst = lds + (wave * G + h0 + k) * ROW;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) dst[d0 + e] = acc[k][e];
+      if (dl == 0) dst[D + 1] = acc[k][VEC];
     }
   }
-
-  // merge the four waves through LDS: [wave][head][D + 2]
-  constexpr int ROW = D + 2;
-  if (tsub == 0) {
+  if (lane == 0) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float* dst = lds + (wave * G + h) * ROW;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) dst[d0 + e] = o[h][e];
-      if (dl == 0) {
-        dst[D] = m[h];
-        dst[D + 1] = l[h];
-      }
-    }
+    for (int h = 0; h < G; ++h) lds[(wave * G + h) * ROW + D] = mg[h];
   }
   row_merge_waves<D, G, OT, NW>(it, a, lds);
 }
@@ -875,7 +970,7 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
   }
 
   // this wave's result for head j: dims 32g + 8r + b from oacc[b][r]
-  constexpr int ROW = D + 2;
+  constexpr int ROW = row_lds_stride(D);
   const float l_tot = group4_sum(l_run);
   if (j < G) {
     float* dst = lds + (wave * G + j) * ROW;
@@ -1530,13 +1625,24 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
 // ---------------------------------------------------------------------------
 
 template <int D, int G, int NW>
-constexpr int row_lds_bytes() { return NW * G * (D + 2) * 4; }
+constexpr int row_lds_bytes() { return NW * G * row_lds_stride(D) * 4; }
 
 // Whether row items of this instantiation can run on the 16x16 MFMA row
 // path (eight or four query heads per KV head, head_dim 128, bf16 or fp8 KV).
 template <int KVT, int D, int G, int QT>
 constexpr bool row_mfma_capable() {
   return (G == 8 || G == 4) && D == 128 && (KVT == KV_BF16 || KVT == KV_FP8) && QT == AUG_BF16;
+}
+
+// The workgroup's item through scalar loads (the address is the same for all
+// its lanes and no kernel writes items), so its fields are scalars and no
+// vector load stands ahead of the block-table and query loads.
+__device__ __forceinline__ WorkItem load_item(const WorkItem* p) {
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  static_assert(sizeof(WorkItem) == 3 * sizeof(u32x4_t), "three 16-byte loads");
+  const auto* src = (const __attribute__((address_space(4))) u32x4_t*)(p);
+  const u32x4_t raw[3] = {src[0], src[1], src[2]};
+  return __builtin_bit_cast(WorkItem, raw);
 }
 
 template <int KVT, int D, int G, int QT, int OT, bool TILES, bool ROW_MFMA, int NW, int F8 = 0>
@@ -1546,7 +1652,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   constexpr int TB = TILES ? TileLds<D>::BYTES : 0;
   static_assert(RB >= 4 && (!TILES || TB >= 4), "a split item's workgroup keeps its merge flag in LDS");
   __shared__ __align__(16) unsigned char smem[RB > TB ? RB : TB];
-  const WorkItem it = a.items[blockIdx.x];
+  const WorkItem it = load_item(a.items + blockIdx.x);
   if constexpr (TILES) {
     if (it.kind == aug::kTileItem) {
       tile_item<KVT, D, G, OT, F8>(it, a, smem);
