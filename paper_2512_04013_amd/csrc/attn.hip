@@ -488,6 +488,8 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
   using elem_t = typename F::raw_t;
 
   const int lane = threadIdx.x & 63;
+  // wave-uniform, so block ids and scales come through scalar loads instead
+  // of queueing behind the K/V loads
   const int wave = threadIdx.x >> 6;
   const int dl = lane % LPT;
   const int tsub = lane / LPT;
@@ -523,8 +525,20 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
   // one is computed.
   constexpr int kWaves = NW;
   const int32_t* table = a.block_ids + it.bt_off + blk0;
-  auto load_block = [&](int bid, elem_t* kr, elem_t* vr) {
+  // fp8: a block's two scales are fetched with its K/V, one block ahead; read
+  // when the block is computed, they cost every block a memory round trip
+  // behind the next block's loads (10 decodes over 49k keys, four heads per KV
+  // head: 33.8 -> 31.4 us; 256 decodes over 418k keys: 182 -> 177 us).
+  struct Scales { float k, v; };
+  auto load_block = [&](int bid, elem_t* kr, elem_t* vr, Scales& sc2) {
     const bool ok = static_cast<uint32_t>(bid) < static_cast<uint32_t>(a.num_pool_blocks);
+    if constexpr (KVT == KV_FP8) {
+      sc2 = Scales{1.f, 1.f};
+      if (ok) {
+        sc2.k = a.k_scale[static_cast<int64_t>(bid) * a.hkv + kvh];
+        sc2.v = a.v_scale[static_cast<int64_t>(bid) * a.hkv + kvh];
+      }
+    }
     const int64_t base = ((static_cast<int64_t>(bid) * a.hkv + kvh) * head_stride + d0) * EB;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
@@ -541,10 +555,11 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
   int bid_next = wave < nblk ? table[wave] : 0;
   elem_t kpre[PREFETCH ? NLD : 1], vpre[PREFETCH ? NLD : 1];
   int bid_pre = 0;
+  Scales spre{1.f, 1.f};
   if constexpr (PREFETCH) {
     if (wave < nblk) {
       bid_pre = __builtin_amdgcn_readfirstlane(bid_next);
-      load_block(bid_pre, kpre, vpre);
+      load_block(bid_pre, kpre, vpre, spre);
       if (wave + kWaves < nblk) bid_next = table[wave + kWaves];
     }
   }
@@ -552,8 +567,10 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
     const int blk = blk0 + bi;
     int bid;
     elem_t kraw[NLD], vraw[NLD];
+    Scales bsc{1.f, 1.f};
     if constexpr (PREFETCH) {
       bid = bid_pre;
+      bsc = spre;
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
         kraw[i] = kpre[i];
@@ -561,21 +578,21 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
       }
       if (bi + kWaves < nblk) {
         bid_pre = __builtin_amdgcn_readfirstlane(bid_next);
-        load_block(bid_pre, kpre, vpre);
+        load_block(bid_pre, kpre, vpre, spre);
         if (bi + 2 * kWaves < nblk) bid_next = table[bi + 2 * kWaves];
       }
     } else {
       bid = __builtin_amdgcn_readfirstlane(bid_next);
       if (bi + kWaves < nblk) bid_next = table[bi + kWaves];
-      load_block(bid, kraw, vraw);
+      load_block(bid, kraw, vraw, bsc);
     }
     const bool bid_ok = static_cast<uint32_t>(bid) < static_cast<uint32_t>(a.num_pool_blocks);
     const int tok0 = blk * kBlock;
     float ksc = sc, vsc = 1.f, vlog = 0.f, vinv = 1.f;
     if constexpr (KVT == KV_FP8) {
       if (bid_ok) {
-        ksc = sc * a.k_scale[static_cast<int64_t>(bid) * a.hkv + kvh];
-        vsc = a.v_scale[static_cast<int64_t>(bid) * a.hkv + kvh];
+        ksc = sc * bsc.k;
+        vsc = bsc.v;
         // bf16 probabilities carry the V scale through its log2 and the row
         // sum weighs it back (a zero scale is taken as 2^-100)
         const float vs = fmaxf(vsc, 0x1p-100f);
