@@ -64,7 +64,7 @@ WORKLOADS = {
 }
 # timed after the main (mixed-batch) workload in the default run, each with its own roofline
 # (a workload name followed by "@valu" runs its row items on the vector ALUs instead of the
-# planner's default, which is MFMA for eight query heads per KV head; "@mfma" runs four-head
+# planner's default, which is MFMA for eight query heads per KV head; "@mfma" runs four-head bf16
 # groups' row items on the MFMA row path, which they take only when asked; "@fp8qk" runs the
 # prefill tiles' score products on fp8 MFMAs and "@fp8" both of their products, opt-in arithmetic)
 DEFAULT_ALSO = ("mixed-8b@mfma", "decode-8b", "decode-8b@mfma", "long-context-8b", "prefill-fp8-64x8",

@@ -150,9 +150,9 @@ typedef struct {
 /* Where the row items (decode rows) of a plan run. Groups of eight or four
  * query heads per KV head with head_dim 128 and bf16 or fp8 KV can run their
  * products on 16x16 bf16 MFMAs; every other shape runs on the vector ALUs.
- * AUTO takes MFMA for groups of eight (the vector ALUs cannot keep up with
- * eight heads of fp8 KV) and VALU otherwise; four-head groups run on MFMA
- * only when asked for. */
+ * AUTO takes MFMA for groups of eight and for groups of four over fp8 KV
+ * (the vector ALUs cannot keep up with the KV stream there) and VALU
+ * otherwise; four-head groups over bf16 KV run on MFMA only when asked for. */
 typedef enum { AUG_ROWS_AUTO = 0, AUG_ROWS_VALU = 1, AUG_ROWS_MFMA = 2 } aug_row_path;
 
 /* Arithmetic of the prefill tiles' products S = Q K^T and O = P V. BF16: Q,

@@ -14,8 +14,8 @@
 //    running (max, sum, output) state; the states are merged across lane
 //    groups with cross-lane swaps and across waves through LDS. Each KV byte
 //    is read once for all G heads (grouped-query sharing). Arithmetic runs on
-//    the vector ALUs in fp32, except for groups of eight (or, when asked for,
-//    four) query heads (bf16 or fp8 KV, head_dim 128), whose products run on
+//    the vector ALUs in fp32, except for groups of eight (or over fp8 KV, and
+//    when asked for, four) query heads (bf16 or fp8 KV, head_dim 128), whose products run on
 //    16x16 bf16 MFMAs with the same item, split and merge structure
 //    (row_item_mfma).
 //  * Tile items (bf16 chunked prefill): 128 query rows (positions x group
@@ -751,8 +751,10 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
 // bf16 dot products of D per head and key) is more than the vector ALUs keep
 // up with next to fp8 decoding, so the eight heads go through 16x16 bf16
 // MFMAs instead (heads 8..15 of each MFMA are zero padding). Groups of four
-// heads take the same path with heads 4..15 as padding: the vector ALUs keep
-// up there, and the MFMA form only frees issue slots for the loads. Per
+// heads take the same path with heads 4..15 as padding: over fp8 KV, where the
+// vector ALUs fall behind as well (177 against 150 us for 256 decodes), by
+// default; over bf16 KV, where they keep up and the MFMA form only frees issue
+// slots for the loads, when asked for. Per
 // 16-token block and wave:
 //   S^T[16 keys][16 heads] = K Q^T with four 16x16x32 MFMAs over head_dim.
 //     Lane l holds token l % 16 and dims 32g .. 32g + 31 (g = l / 16) of the
