@@ -1009,7 +1009,7 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
 // tile items (bf16 MFMA)
 // ---------------------------------------------------------------------------
 
-template <int D>
+template <int D, bool DMA>
 struct TileLds {
   static constexpr int KS = D + 8;    // K row stride (elements): 16-byte aligned, conflict-free reads
   static constexpr int KS8 = D + 16;  // K row stride (bytes) of fp8 keys kept as codes
@@ -1019,7 +1019,10 @@ struct TileLds {
   // V row stride (elements): rows 64 bytes apart modulo the 256-byte bank
   // width, so the transposing reads of four consecutive rows hit distinct banks
   static constexpr int VS = D + 32;
-  static constexpr int STAGE = 64 * (KS + VS) * 2;       // bytes of one K + V stage
+  // bf16 keys and values come by direct loads, rows of D elements without
+  // padding, K then V (see tile_chunk); fp8 ones through registers, padded
+  static constexpr int ROW = D * 2;                       // bytes of an unpadded row
+  static constexpr int STAGE = DMA ? 128 * ROW : 64 * (KS + VS) * 2;   // bytes of one K + V stage
   static constexpr int IDS = aug::kTileSpanMax / kBlock + 8; // block ids of one item's key span
   // fp8, per stage and block of the tile: the K scale times the softmax
   // coefficient, log2 of the V scale, and the V scale's reciprocal
@@ -1027,7 +1030,28 @@ struct TileLds {
   static constexpr int SCALES = 2 * NSC * 4;
   static constexpr int BYTES = 2 * STAGE + IDS * 4 + SCALES;
   static_assert(D * VT8 <= 64 * VS * 2, "transposed fp8 values fit the V region of a stage");
+  static_assert(!DMA || 2 * STAGE <= 65536, "direct loads address a stage with 16 bits");
 };
+
+// Direct loads fill LDS in order (lane l of an instruction writes bytes 16 l ..
+// of 1 KiB), so rows cannot be padded against bank conflicts; instead the
+// 16-byte chunk c of row r sits at chunk c ^ tile_chunk(r) of its row, and the
+// loads permute which chunk each lane fetches. Sixteen rows at one column (the
+// K operands) and four rows at four neighbouring columns (the transposing V
+// reads) then fall on distinct banks.
+template <int D>
+__device__ __forceinline__ int tile_chunk(int r) {
+  return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
+
+// 16 bytes per lane from base + off to LDS byte address lds + 16 * lane, without
+// passing through registers. The wave's own s_waitcnt vmcnt(0) completes it;
+// the compiler does not see the load (a builtin would make it wait before every
+// LDS read that might alias), its own counts only wait for more than they must.
+__device__ __forceinline__ void load_to_lds16(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds), "v"(off), "s"(base) : "memory");
+}
 
 // Staging of one thread's share of a key tile: 16-byte bf16 chunks, or
 // 8-byte fp8 chunks converted (exactly) to bf16 on the way into LDS.
@@ -1086,10 +1110,11 @@ template <bool B> using bool_tag = std::integral_constant<bool, B>;
 // P V on fp8 MFMAs (probabilities rounded to E4M3, values as stored).
 template <int KVT, int D, int G, int OT, int F8>
 __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* smem) {
-  using L = TileLds<D>;
   using TS = TileStage<KVT>;
   using raw_t = typename TS::raw_t;
   constexpr bool FP8 = KVT == KV_FP8;
+  constexpr bool DMA = !FP8;          // bf16 K/V go straight to LDS
+  using L = TileLds<D, DMA>;
   constexpr bool QK8 = F8 >= 1;
   constexpr bool PV8 = F8 >= 2;
   static_assert(!QK8 || (FP8 && D == 128), "fp8 score products need fp8 keys and head_dim 128");
@@ -1241,7 +1266,7 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     // and its values, at most 2^-8 of the item's largest, are left out.
     vsmall = vref * 0x1p-8f;
   }
-  const int t_full = bad ? t0 : max(t0, min(t1, min(it.pos0 + 1, key_end) / 64));
+  const int t_full = bad && !DMA ? t0 : max(t0, min(t1, min(it.pos0 + 1, key_end) / 64));
 
   // a thread stages KPT consecutive keys of one block (KPT divides 16)
   raw_t kr[KPT], vr[KPT];
@@ -1360,18 +1385,71 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     }
   };
 
+  // direct loads: wave w fetches block w of a key tile, RPI rows an instruction
+  constexpr int RPI = 1024 / L::ROW;
+  const int dma_wave = __builtin_amdgcn_readfirstlane(wave);
+  const int dma_row = lane * 16 / L::ROW;            // row within an instruction
+  const uint32_t dma_off = dma_row * L::ROW + (((lane & (L::ROW / 16 - 1)) ^ tile_chunk<D>(dma_row)) << 4);
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+      (__attribute__((address_space(3))) unsigned char*)(smem)));
+  int dma_bid = -1;                                   // the block in flight, -1 if none was loaded
+  auto issue_tile = [&](int t, int stage) {
+    const int tok0 = t * 64 + 16 * dma_wave;
+    const int bid = __builtin_amdgcn_readfirstlane(tok0 < key_end ? ids[(tok0 >> 4) - blk_first] : -1);
+    dma_bid = static_cast<uint32_t>(bid) < static_cast<uint32_t>(a.num_pool_blocks) ? bid : -1;
+    if (dma_bid < 0) return;
+    const int64_t base = (static_cast<int64_t>(bid) * a.hkv + kvh) * head_stride * EB;
+    const uint32_t dst = lds0 + stage * L::STAGE + dma_wave * 16 * L::ROW;
+#pragma unroll
+    for (int i = 0; i < 16 / RPI; ++i) {
+      // rows RPI i ..: the chunk permutation of row dma_row, with i's own bits
+      const uint32_t off = i * 1024 + (dma_off ^ (tile_chunk<D>(RPI * i) << 4));
+      load_to_lds16(kc + base, off, dst + i * 1024);
+      load_to_lds16(vc + base, off, dst + 64 * L::ROW + i * 1024);
+    }
+  };
+  // This wave's part of tile t is complete: its loads have landed, and rows
+  // past the span or of a block outside the pool read as zero.
+  auto settle_tile = [&](int t, int stage) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int tok0 = t * 64 + 16 * dma_wave;
+    if (dma_bid < 0 || tok0 + 16 > key_end) {
+      const int first = dma_bid < 0 ? 0 : key_end - tok0;
+      unsigned char* dst = smem + stage * L::STAGE + dma_wave * 16 * L::ROW;
+#pragma unroll
+      for (int i = 0; i < 16 / RPI; ++i)
+        if (RPI * i + dma_row >= first) {
+          *reinterpret_cast<uint4*>(dst + i * 1024 + lane * 16) = uint4{0, 0, 0, 0};
+          *reinterpret_cast<uint4*>(dst + 64 * L::ROW + i * 1024 + lane * 16) = uint4{0, 0, 0, 0};
+        }
+    }
+  };
+  // operand addresses of the direct layout in a stage: chunk hh of K row n
+  // (rows n and n + 32 share a permutation), and the row and columns of
+  // v_lane_off in V; the other chunks are exclusive-ors away
+  const uint32_t k_lane = n * L::ROW + ((hh ^ tile_chunk<D>(n)) << 4);
+  const int v_row = 4 * hh + (lane & 15) / 4;
+  const uint32_t v_lane = 64 * L::ROW + v_row * L::ROW +
+                          (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ tile_chunk<D>(v_row)) << 4) + 8 * (lane & 1);
+
   auto step = [&](int t, auto mask_tag) {
     constexpr bool MASK = decltype(mask_tag)::value;
     const int k0 = t * 64;
     const int stage = (t - t0) & 1;
+    if constexpr (DMA) settle_tile(t, stage);
     __syncthreads();   // stage `stage` is written; the other stage's readers are done
     if (t + 1 < t1) {
-      store_tile(stage ^ 1);
-      if (t + 2 < t1) {
-        if (t + 2 < t_full) load_tile(k0 + 128, bool_tag<true>{});
-        else load_tile(k0 + 128, bool_tag<false>{});
+      if constexpr (DMA) {
+        issue_tile(t + 1, stage ^ 1);
+      } else {
+        store_tile(stage ^ 1);
+        if (t + 2 < t1) {
+          if (t + 2 < t_full) load_tile(k0 + 128, bool_tag<true>{});
+          else load_tile(k0 + 128, bool_tag<false>{});
+        }
       }
     }
+    const uint32_t k_base = k_lane + stage * L::STAGE, v_base = v_lane + stage * L::STAGE;
     const uint16_t* ks = reinterpret_cast<const uint16_t*>(smem + stage * L::STAGE);
     const uint16_t* vs = ks + 64 * L::KS;
 
@@ -1410,7 +1488,8 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
       for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s)
-          kop[mb][s] = *reinterpret_cast<const uint4*>(ks + (32 * mb + n) * L::KS + 16 * s + 8 * hh);
+          kop[mb][s] = DMA ? *reinterpret_cast<const uint4*>(smem + (k_base ^ (32 * s)) + 32 * mb * L::ROW)
+                           : *reinterpret_cast<const uint4*>(ks + (32 * mb + n) * L::KS + 16 * s + 8 * hh);
       __builtin_amdgcn_sched_barrier(0);
       // back to normal issue priority for the matrix work (raised below)
       __builtin_amdgcn_s_setprio(0);
@@ -1450,8 +1529,13 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
           const uint16_t* v0 = vs + (16 * s) * L::VS + 32 * db + v_lane_off;
+          const uint16_t* v1 = v0 + 8 * L::VS;
+          if constexpr (DMA) {
+            v0 = reinterpret_cast<const uint16_t*>(smem + (v_base ^ (64 * db)) + 16 * s * L::ROW);
+            v1 = reinterpret_cast<const uint16_t*>(smem + (v_base ^ (64 * db + 32)) + (16 * s + 8) * L::ROW);
+          }
           const uint2 lo = ds_read_tr16(v0);
-          const uint2 hi = ds_read_tr16(v0 + 8 * L::VS);
+          const uint2 hi = ds_read_tr16(v1);
           vop[s][db] = uint4{lo.x, lo.y, hi.x, hi.y};
         }
     }
@@ -1585,14 +1669,18 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     __builtin_amdgcn_s_setprio(1);
   };
 
-  if (t0 < t_full) load_tile(t0 * 64, bool_tag<true>{});
-  else load_tile(t0 * 64, bool_tag<false>{});
-  store_tile(0);
-  if (t0 + 1 < t1) {
-    if (t0 + 1 < t_full) load_tile((t0 + 1) * 64, bool_tag<true>{});
-    else load_tile((t0 + 1) * 64, bool_tag<false>{});
-  }
   int t = t0;
+  if constexpr (DMA) {
+    issue_tile(t0, 0);
+  } else {
+    if (t0 < t_full) load_tile(t0 * 64, bool_tag<true>{});
+    else load_tile(t0 * 64, bool_tag<false>{});
+    store_tile(0);
+    if (t0 + 1 < t1) {
+      if (t0 + 1 < t_full) load_tile((t0 + 1) * 64, bool_tag<true>{});
+      else load_tile((t0 + 1) * 64, bool_tag<false>{});
+    }
+  }
   for (; t < t_full; ++t) step(t, bool_tag<false>{});
   for (; t < t1; ++t) step(t, bool_tag<true>{});
 
@@ -1668,7 +1756,7 @@ template <int KVT, int D, int G, int QT, int OT, bool TILES, bool ROW_MFMA, int 
 __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   static_assert(!TILES || NW == kThreads / 64, "tile items run on four-wave workgroups");
   constexpr int RB = row_lds_bytes<D, G, NW>();
-  constexpr int TB = TILES ? TileLds<D>::BYTES : 0;
+  constexpr int TB = TILES ? TileLds<D, KVT != KV_FP8>::BYTES : 0;
   static_assert(RB >= 4 && (!TILES || TB >= 4), "a split item's workgroup keeps its merge flag in LDS");
   __shared__ __align__(16) unsigned char smem[RB > TB ? RB : TB];
   const WorkItem it = load_item(a.items + blockIdx.x);
