@@ -57,6 +57,8 @@ using aug::kBlock;
 using aug::MergeGroup;
 using aug::WorkItem;
 
+template <bool B> using bool_tag = std::integral_constant<bool, B>;
+
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef int v8i_t __attribute__((ext_vector_type(8)));   // 32 fp8 codes: one 32x32x64 MFMA operand
@@ -142,6 +144,20 @@ __device__ __forceinline__ float group_sum(float v) {
 // ---------------------------------------------------------------------------
 // KV element formats for the row path
 // ---------------------------------------------------------------------------
+
+// Loads of K/V that the launch reads once. STREAM marks them non-temporal, so
+// that they leave the caches to the data that is read again: on launches that
+// read more than the caches hold (plan_format.h, WorkItem::stream) the same
+// loads then run at 6.4 TB/s instead of 5.8 (256 decodes over 418k keys, bf16,
+// 295 -> 268 us). Smaller launches find part of their K/V in the 256 MB
+// last-level cache and lose up to a quarter by it.
+template <bool STREAM, typename T>
+__device__ __forceinline__ T load_kv(const char* p) {
+  typedef uint32_t vec_t __attribute__((ext_vector_type(sizeof(T) / 4)));
+  const vec_t* q = reinterpret_cast<const vec_t*>(p);
+  if constexpr (STREAM) return __builtin_bit_cast(T, __builtin_nontemporal_load(q));
+  else return __builtin_bit_cast(T, *q);
+}
 
 template <int KVT> struct KvFmt;
 template <> struct KvFmt<KV_F32> {
@@ -475,7 +491,7 @@ __device__ __forceinline__ void lane_sum(float (*v)[N]) {
 }
 
 
-template <int KVT, int D, int G, int QT, int OT, bool PREFETCH, int NW>
+template <int KVT, int D, int G, int QT, int OT, bool PREFETCH, int NW, bool STREAM>
 __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
   using F = KvFmt<KVT>;
   using M = RowMath<KVT, QT>;
@@ -544,8 +560,8 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
     for (int i = 0; i < NLD; ++i) {
       if (ok) {
         const int64_t off = base + static_cast<int64_t>(i * TPI + tsub) * D * EB;
-        kr[i] = *reinterpret_cast<const elem_t*>(kc + off);
-        vr[i] = *reinterpret_cast<const elem_t*>(vc + off);
+        kr[i] = load_kv<STREAM, elem_t>(kc + off);
+        vr[i] = load_kv<STREAM, elem_t>(vc + off);
       } else {
         kr[i] = elem_t{};
         vr[i] = elem_t{};
@@ -757,8 +773,9 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
 // slots for the loads, when asked for. Per
 // 16-token block and wave:
 //   S^T[16 keys][16 heads] = K Q^T with four 16x16x32 MFMAs over head_dim.
-//     Lane l holds token l % 16 and dims 32g .. 32g + 31 (g = l / 16) of the
-//     block's K rows; k-step s takes dims 32g + 8s .. + 8 of both K and Q (a
+//     Lane l holds token l % 16 and 32 dims of the block's K rows, 16 bytes of
+//     every 64 (the four lane groups g = l / 16 of one load cover whole 64-byte
+//     pieces); a k-step takes the same eight dims of K and Q in each lane (a
 //     permutation of the reduction dimension shared by both operands).
 //   The S^T accumulator gives lane l head l % 16 and keys 4g .. 4g + 3, which
 //   is exactly the B operand layout of a 16x16x16 MFMA over those keys, so
@@ -787,18 +804,29 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 
+// A value at a wave-uniform address that no kernel of the launch writes: a
+// scalar load, which neither queues behind the K/V loads nor counts with them.
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T* p) {
+  return *(const __attribute__((address_space(4))) T*)(p);
+}
+
 template <int KVT> struct MfmaRowKv;
 template <> struct MfmaRowKv<KV_BF16> {
-  struct K { uint4 w[4]; };      // token l % 16, dims 32g .. 32g + 31
+  struct K { uint4 w[4]; };      // token l % 16, dims 32i + 8g .. + 7
   struct V { uint4 w[4]; };      // tokens 4g + t, dims 8m .. 8m + 7
   static constexpr int EB = 2;
+  // first of the eight dims of k-step s in lane group g
+  __device__ static constexpr int k_dim(int s, int g) { return 32 * s + 8 * g; }
+  template <bool S>
   __device__ static void load_k(const char* p, K& k) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) k.w[i] = reinterpret_cast<const uint4*>(p)[i];
+    for (int i = 0; i < 4; ++i) k.w[i] = load_kv<S, uint4>(p + 64 * i);
   }
+  template <bool S>
   __device__ static void load_v(const char* p, int64_t row_bytes, V& v) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) v.w[t] = *reinterpret_cast<const uint4*>(p + t * row_bytes);
+    for (int t = 0; t < 4; ++t) v.w[t] = load_kv<S, uint4>(p + t * row_bytes);
   }
   __device__ static uint4 k_operand(const K& k, int s) { return k.w[s]; }
   __device__ static void zero_v(V& v, int t) { v.w[t] = uint4{0, 0, 0, 0}; }
@@ -816,16 +844,19 @@ template <> struct MfmaRowKv<KV_BF16> {
   }
 };
 template <> struct MfmaRowKv<KV_FP8> {
-  struct K { uint4 w[2]; };
+  struct K { uint4 w[2]; };      // token l % 16, dims 64i + 16g .. + 15
   struct V { uint2 w[4]; };
   static constexpr int EB = 1;
+  __device__ static constexpr int k_dim(int s, int g) { return 64 * (s >> 1) + 16 * g + 8 * (s & 1); }
+  template <bool S>
   __device__ static void load_k(const char* p, K& k) {
-    k.w[0] = reinterpret_cast<const uint4*>(p)[0];
-    k.w[1] = reinterpret_cast<const uint4*>(p)[1];
+    k.w[0] = load_kv<S, uint4>(p);
+    k.w[1] = load_kv<S, uint4>(p + 64);
   }
+  template <bool S>
   __device__ static void load_v(const char* p, int64_t row_bytes, V& v) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) v.w[t] = *reinterpret_cast<const uint2*>(p + t * row_bytes);
+    for (int t = 0; t < 4; ++t) v.w[t] = load_kv<S, uint2>(p + t * row_bytes);
   }
   __device__ static uint4 k_operand(const K& k, int s) {
     const uint4& w = k.w[s >> 1];
@@ -853,7 +884,7 @@ template <> struct MfmaRowKv<KV_FP8> {
   }
 };
 
-template <int KVT, int OT, int NW, int G>
+template <int KVT, int OT, int NW, int G, bool STREAM>
 __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds) {
   static_assert(G == 8 || G == 4, "one 16-column MFMA holds the group's heads");
   constexpr int D = 128;
@@ -868,13 +899,14 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
   const int g = lane >> 4;            // keys 4g .. 4g + 3 of a block
   const int kvh = it.kvh;
 
-  // Q^T operands of the four k-steps: dims 32g + 8s .. + 8 of head j
+  // Q^T operands of the four k-steps: dims k_dim(s, g) .. + 7 of head j
   uint4 qop[4];
   {
     const uint16_t* qb = static_cast<const uint16_t*>(a.q) +
-                         (static_cast<int64_t>(it.q_row0) * a.hq + static_cast<int64_t>(kvh) * G + (j < G ? j : 0)) * D + 32 * g;
+                         (static_cast<int64_t>(it.q_row0) * a.hq + static_cast<int64_t>(kvh) * G + (j < G ? j : 0)) * D;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) qop[s] = j < G ? *reinterpret_cast<const uint4*>(qb + 8 * s) : uint4{0, 0, 0, 0};
+    for (int s = 0; s < 4; ++s)
+      qop[s] = j < G ? *reinterpret_cast<const uint4*>(qb + KV::k_dim(s, g)) : uint4{0, 0, 0, 0};
   }
   const float sc = a.scale_log2;
   float m_run = kNegBig, l_run = 0.f;
@@ -888,7 +920,7 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
   constexpr int64_t kHead = kBlock * kRow;                               // bytes of one (block, head)
   const char* kc = static_cast<const char*>(a.k_cache);
   const char* vc = static_cast<const char*>(a.v_cache);
-  const int64_t k_lane = (j * D + 32 * g) * EB;                          // token j, dims 32g..
+  const int64_t k_lane = j * kRow + 16 * g;                              // token j, 16 bytes of each 64
   const int64_t v_lane = (4 * g * D + 8 * j) * EB;                       // tokens 4g.., dims 8j..
   constexpr int kWaves = NW;
   const int32_t* table = a.block_ids + it.bt_off + blk0;
@@ -898,11 +930,11 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
   auto load_block = [&](int bid, typename KV::K& k, typename KV::V& v, Scales& sc2) {
     if (static_cast<uint32_t>(bid) < static_cast<uint32_t>(a.num_pool_blocks)) {
       const int64_t base = (static_cast<int64_t>(bid) * a.hkv + kvh) * kHead;
-      KV::load_k(kc + base + k_lane, k);
-      KV::load_v(vc + base + v_lane, kRow, v);
+      KV::template load_k<STREAM>(kc + base + k_lane, k);
+      KV::template load_v<STREAM>(vc + base + v_lane, kRow, v);
       if constexpr (FP8) {
-        sc2.k = a.k_scale[static_cast<int64_t>(bid) * a.hkv + kvh];
-        sc2.v = a.v_scale[static_cast<int64_t>(bid) * a.hkv + kvh];
+        sc2.k = load_uniform(a.k_scale + static_cast<int64_t>(bid) * a.hkv + kvh);
+        sc2.v = load_uniform(a.v_scale + static_cast<int64_t>(bid) * a.hkv + kvh);
       }
     } else {
       k = typename KV::K{};
@@ -911,29 +943,32 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
     }
   };
 
-  // the next block's K/V (and scales) in flight while one is computed, its
-  // id read one iteration before that (deeper prefetch measured no faster)
-  typename KV::K kpre{};
-  typename KV::V vpre{};
-  Scales spre{1.f, 1.f};
-  int bid_pre = wave < nblk ? __builtin_amdgcn_readfirstlane(table[wave]) : 0;
-  if (wave < nblk) load_block(bid_pre, kpre, vpre, spre);
-  int bid_next = wave + kWaves < nblk ? table[wave + kWaves] : 0;
-  for (int bi = wave; bi < nblk; bi += kWaves) {
+  // Blocks come in two register sets that take turns, so nothing is copied from
+  // one to the other (a loop that moved the prefetched set into the computed one
+  // spent 120 moves a block), and two blocks share a round trip to memory: the
+  // loads of the second are issued before the first is waited for. Block ids
+  // and scales are scalar loads. With the streamed loads above: 512 fp8 decodes
+  // over 1.7 M keys, 621 -> 573 us; 40 over 160k keys 70 -> 68.
+  struct Block {
+    typename KV::K k{};
+    typename KV::V v{};
+    Scales sc{1.f, 1.f};
+    int bid = -1;
+  };
+  int bid_next = wave < nblk ? load_uniform(table + wave) : -1;
+  // fetch block bi if the span has it, and the id of the one after
+  auto fetch = [&](int bi, Block& b) {
+    if (bi >= nblk) return;
+    b.bid = bid_next;
+    load_block(b.bid, b.k, b.v, b.sc);
+    if (bi + kWaves < nblk) bid_next = load_uniform(table + bi + kWaves);
+  };
+  auto compute = [&](int bi, Block& blk) {
     const int tok0 = (blk0 + bi) * kBlock;
-    const int bid = bid_pre;
-    typename KV::K kraw = kpre;
-    typename KV::V vraw = vpre;
-    const Scales bsc = spre;
-    // the next block's loads are issued ahead of the other waves' work on
-    // this SIMD (measured 1-2 % on decode batches)
-    __builtin_amdgcn_s_setprio(1);
-    if (bi + kWaves < nblk) {
-      bid_pre = __builtin_amdgcn_readfirstlane(bid_next);
-      load_block(bid_pre, kpre, vpre, spre);
-      if (bi + 2 * kWaves < nblk) bid_next = table[bi + 2 * kWaves];
-    }
-    __builtin_amdgcn_s_setprio(0);
+    const int bid = blk.bid;
+    const typename KV::K& kraw = blk.k;
+    typename KV::V& vraw = blk.v;
+    const Scales& bsc = blk.sc;
     const bool bid_ok = static_cast<uint32_t>(bid) < static_cast<uint32_t>(a.num_pool_blocks);
     float ksc = sc, vlog = 0.f, vinv = 1.f;
     if constexpr (FP8) {
@@ -986,6 +1021,21 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
 #pragma unroll
     for (int b = 0; b < 8; ++b)
       oacc[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, vop[b]), pop, oacc[b], 0, 0, 0);
+  };
+  Block b0, b1;
+  fetch(wave, b0);
+  for (int bi = wave; bi < nblk; bi += 2 * kWaves) {
+    // loads are issued ahead of the other waves' work on this SIMD (measured
+    // 1-2 % on decode batches)
+    __builtin_amdgcn_s_setprio(1);
+    fetch(bi + kWaves, b1);
+    __builtin_amdgcn_s_setprio(0);
+    compute(bi, b0);
+    if (bi + kWaves >= nblk) break;
+    __builtin_amdgcn_s_setprio(1);
+    fetch(bi + 2 * kWaves, b0);
+    __builtin_amdgcn_s_setprio(0);
+    compute(bi + kWaves, b1);
   }
 
   // this wave's result for head j: dims 32g + 8r + b from oacc[b][r]
@@ -1093,8 +1143,6 @@ __device__ __forceinline__ float sum_across_halves(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-
-template <bool B> using bool_tag = std::integral_constant<bool, B>;
 
 // One tile item: up to 128 query rows (kTileRows / G positions x G heads of
 // one KV head) against keys [key_begin, key_end) of the request. Key tiles of
@@ -1768,10 +1816,14 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   }
   // row items always fetch a wave's next block while the current one is
   // computed: short spans (small batches) are latency bound otherwise
-  if constexpr (ROW_MFMA && row_mfma_capable<KVT, D, G, QT>())
-    row_item_mfma<KVT, OT, NW, G>(it, a, reinterpret_cast<float*>(smem));
-  else
-    row_item<KVT, D, G, QT, OT, true, NW>(it, a, reinterpret_cast<float*>(smem));
+  float* lds = reinterpret_cast<float*>(smem);
+  auto row = [&](auto stream_tag) {
+    constexpr bool S = decltype(stream_tag)::value;
+    if constexpr (ROW_MFMA && row_mfma_capable<KVT, D, G, QT>()) row_item_mfma<KVT, OT, NW, G, S>(it, a, lds);
+    else row_item<KVT, D, G, QT, OT, true, NW, S>(it, a, lds);
+  };
+  if (it.stream) row(bool_tag<true>{});
+  else row(bool_tag<false>{});
 }
 
 // Batches without prefill tiles: row items only, on workgroups of NW waves.

@@ -256,6 +256,8 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
       return fail(AUG_ERR_INVALID, "%s: block %d receives new tokens more than once", who, *dup);
   }
 
+  const int32_t kv_elem = s->kv_dtype == AUG_F32 ? 4 : s->kv_dtype == AUG_BF16 ? 2 : 1;
+  const bool stream = total_row_keys * s->head_dim * kv_elem * 2 >= kStreamBytes;
   // a launch without tiles runs MFMA row items on eight-wave workgroups
   const int32_t split = choose_split(total_row_keys, kv_split_tokens, !any_tiled && row_path == AUG_ROWS_MFMA, !any_tiled);
   const int32_t pos_per_tile = kTileRows / g;
@@ -491,6 +493,7 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
           WorkItem it{};
           it.kvh = static_cast<int16_t>(h);
           it.kind = kRowItem;
+          it.stream = stream ? 1 : 0;
           it.q_row0 = b->q_start[r] + j;
           it.n_rows = 1;
           it.part_stride = 1;

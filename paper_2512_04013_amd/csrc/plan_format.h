@@ -13,6 +13,13 @@ constexpr int32_t kKeyTile = 64;            // keys per MFMA tile (4 blocks)
 constexpr int32_t kTileRows = 128;          // query rows (positions x group heads) per MFMA tile
 constexpr int32_t kTileSpanMin = 256;       // a tile is never split into spans shorter than this
 constexpr int32_t kTileSpanMax = 8192;      // longest key span of one tile item (its block ids fit in LDS)
+// Row items of a launch that read at least this much K/V load it past the
+// caches. Measured with three batches in turn, 32 decodes of equal contexts, K/V
+// bytes of one launch, cached against streamed: bf16 48 MB 11.8 / 12.7 us,
+// 64 MB 17.3 / 17.3, 96 MB 21.4 / 21.2, 128 MB 33.1 / 29.3; fp8 64 MB 17.0 /
+// 21.7, 96 MB 22.5 / 24.0, 128 MB 31.2 / 29.7. From there up streaming wins by
+// 8 to 11 % (the last-level cache holds 256 MB).
+constexpr int64_t kStreamBytes = 100'000'000;
 constexpr int32_t kMaxContext = 1 << 24;    // longest context of one request the planner accepts
 constexpr int32_t kMaxSplit = 1 << 24;      // largest requested decode split (keys per work item)
 
@@ -50,7 +57,7 @@ struct PlanHeader {          // 64 bytes
 struct WorkItem {            // 48 bytes
   int16_t kvh;               // KV head
   int8_t kind;               // ItemKind
-  int8_t reserved0;
+  int8_t stream;             // row items: 1 if their K/V loads leave the caches alone (see kStreamBytes)
   int32_t q_row0;            // first global row of Q/O
   int16_t n_rows;            // rows (context positions) in the item
   int16_t part_stride;       // tiles: distance between the partial slots of consecutive rows
