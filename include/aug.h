@@ -129,7 +129,10 @@ typedef struct {
   int32_t num_merge_groups;  /* split (row, KV head) pairs; the first num_tile_merge_groups
                                 belong to prefill tiles */
   int32_t num_partials;      /* split-K partial results */
-  int32_t kv_split_tokens;   /* keys per decode work item (multiple of block_size) */
+  int32_t kv_split_tokens;   /* the requested split, or the planner's split by size: keys per decode
+                                work item (multiple of block_size). Unless a split was requested,
+                                items of small batches may be cut longer or shorter than it,
+                                where that fills the GPU better */
   int32_t total_rows;        /* q_start[num_reqs] */
   int32_t num_reqs;
   int32_t num_tile_merge_groups;

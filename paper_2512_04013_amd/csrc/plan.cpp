@@ -143,6 +143,180 @@ int32_t choose_split(int64_t total_row_keys, int32_t requested, bool wide_rows, 
   return static_cast<int32_t>(((s + kBlock - 1) / kBlock) * kBlock);
 }
 
+// Split of the row items by estimated launch time. With few items a launch is
+// a handful of rounds over the resident workgroups, and whether the last round
+// is full or nearly empty matters more than any per-key rate: 1000 items of 480
+// keys on 512 slots take two rounds where 500 items of twice the keys take one
+// (18 fp8 decodes of 1700 keys beside a 45-row chunk, 64/8 heads: 37.3 -> 31.1
+// us); short contexts on an idle card want spans down to 128 keys (16 fp32
+// decodes of 400 keys 20.2 -> 10.3 us). So each candidate split is priced by
+// list scheduling, longest item first as the kernel's order has it, of
+//   row items:  kRowFixed + blocks per wave * block time (+ kRowSplit if split)
+//   tile items: kTileFixed + steps * tile step
+// plus kPerItem for every item, and never below the K/V at the memory's rate. A
+// block's time is the path's latency per block or its share of the memory rate.
+// Calibrated on 45 batches (the small and middle sizes of every layer shape)
+// at 16 splits each: the split that this picks is within 4 % of the best one in
+// the mean, where one eighth of total keys per CU, at least 512, was 13 % off.
+constexpr double kRowFixed = 2500, kRowSplit = 1600, kTileFixed = 4500, kPerItem = 4;   // ns
+constexpr double kCachedRate = 9000, kMemoryRate = 6400;                                // bytes per ns
+constexpr int32_t kSplits[] = {128, 192, 256, 384, 512, 768, 1024, 1280, 1536, 2048, 3072, 4096, 6144, 8192};
+constexpr int32_t kMaxIters = 8192 / kBlock;
+
+double block_latency_ns(const aug_attn_shape& s, bool mfma) {
+  if (s.head_dim == 64) return s.kv_dtype == AUG_F32 ? 400 : 550;
+  if (s.kv_dtype == AUG_F32) return 1700;
+  if (s.kv_dtype == AUG_BF16) return 950;
+  return mfma ? 630 : 1000;
+}
+double tile_step_ns(const aug_attn_shape& s) { return s.head_dim == 64 ? 1100 : 2000; }
+
+using Durations = std::vector<std::pair<double, int64_t>>;   // (ns, number of items)
+
+// Makespan of the items on `slots` slots, longest first. Slots that are free at
+// the same time are kept as one entry, so the cost is per distinct duration.
+double list_schedule(Durations& d, int64_t slots, std::vector<std::pair<double, int64_t>>& heap) {
+  std::sort(d.begin(), d.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  const auto later = [](const auto& a, const auto& b) { return a.first > b.first; };
+  heap.assign(1, {0.0, slots});
+  double end = 0.0;
+  for (auto [ns, count] : d) {
+    while (count > 0) {
+      std::pop_heap(heap.begin(), heap.end(), later);
+      const auto [at, n] = heap.back();
+      heap.pop_back();
+      const int64_t k = std::min(n, count);
+      if (n > k) {
+        heap.emplace_back(at, n - k);
+        std::push_heap(heap.begin(), heap.end(), later);
+      }
+      heap.emplace_back(at + ns, k);
+      std::push_heap(heap.begin(), heap.end(), later);
+      end = std::max(end, at + ns);
+      count -= k;
+    }
+  }
+  return end;
+}
+
+// Near-equal spans of whole blocks for `keys` keys at split `split`.
+int32_t row_span(int32_t keys, int32_t split) {
+  const int32_t n = (keys + split - 1) / split;
+  return (((keys + n - 1) / n + kBlock - 1) / kBlock) * kBlock;
+}
+
+struct TileSpans {
+  int32_t span, count;
+};
+
+// Near-equal spans of whole key tiles for a tile item that reads `keys` keys.
+TileSpans tile_spans(int32_t keys, int32_t limit) {
+  const int32_t n = (keys + limit - 1) / limit;
+  const int32_t span = (((keys + n - 1) / n + kKeyTile - 1) / kKeyTile) * kKeyTile;
+  return {span, (keys + span - 1) / span};
+}
+
+struct RowLoad {           // rows that become row items
+  int32_t q, ctx;          // rows of the request and its context
+};
+
+// The split of the row items when the caller leaves it to the planner. `before`
+// is the split that prefill tiles were cut against and `tiles` their items.
+// Launches with many items keep a rule on sizes (their rounds even out): spans
+// of one slot's share of all keys, up to the same cap.
+int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows, const Durations& tiles,
+                      int64_t total_row_keys, int32_t before, bool mfma, bool wide_rows, bool rows_only,
+                      int64_t tile_partials) {
+  if (rows.empty()) return before;
+  const int32_t hkv = s.num_kv_heads;
+  const int32_t g = s.num_q_heads / hkv;
+  const int32_t waves = wide_rows ? 8 : 4;
+  // bf16 rows in eight waves leave room for one workgroup a CU
+  const int64_t slots = wide_rows && s.kv_dtype == AUG_BF16 ? kSlots / 2 : kSlots;
+  const int64_t block_bytes = int64_t{2} * kBlock * s.head_dim * (s.kv_dtype == AUG_F32 ? 4 : s.kv_dtype == AUG_BF16 ? 2 : 1);
+  const int64_t bytes = total_row_keys * block_bytes / kBlock;
+  int64_t n_tiles = 0;
+  for (const auto& t : tiles) n_tiles += t.second;
+  int64_t parts = 0;
+  const auto count = [&](int32_t split) {      // items, and partials in `parts`
+    int64_t n = n_tiles;
+    parts = 0;
+    for (const RowLoad& r : rows) {
+      const int32_t span = row_span(r.ctx, split);
+      for (int32_t j = 0; j < r.q; ++j) {
+        const int64_t k = (r.ctx - r.q + j + span) / span;     // spans of position ctx - q + j
+        n += k * hkv;
+        parts += k > 1 ? k * hkv : 0;
+      }
+    }
+    return n;
+  };
+  const int64_t n_before = count(before);
+  const int64_t parts_before = parts;
+  constexpr int64_t kManyItems = 4 * kSlots;
+  if (n_before >= kManyItems) {
+    const int64_t cap = wide_rows ? 8192 : rows_only ? 6144 : 4096;
+    const int64_t share = std::min(cap, (total_row_keys + kSlots - 1) / kSlots);
+    return std::max<int32_t>(before, static_cast<int32_t>((share + kBlock - 1) / kBlock * kBlock));
+  }
+  // a batch that fits the library's own scratch array keeps fitting it
+  const int64_t part_bytes = partial_floats(g, s.head_dim) * 4;
+  const int64_t max_parts =
+      std::max<int64_t>(parts_before, static_cast<int64_t>(AUG_NOALLOC_SCRATCH_BYTES) / part_bytes - tile_partials - 1);
+  const double rate = bytes >= kStreamBytes ? kMemoryRate : kCachedRate;
+  const double latency = block_latency_ns(s, mfma);
+  int32_t longest = 0;
+  for (const RowLoad& r : rows) longest = std::max(longest, r.ctx);
+
+  std::vector<int64_t> whole(kMaxIters + 1), split_items(kMaxIters + 1);
+  Durations d, heap;
+  int32_t best = before;
+  double best_ns = -1.0;
+  const auto price = [&](int32_t split) {
+    const int64_t n = count(split);
+    if (n >= kManyItems || parts > max_parts) return;
+    const double active = static_cast<double>(std::min<int64_t>(slots, n));
+    const double block_ns = std::max(latency, active * waves * static_cast<double>(block_bytes) / rate);
+    const auto iters = [&](int32_t keys) {
+      return std::min<int32_t>(kMaxIters, ((keys + kBlock - 1) / kBlock + waves - 1) / waves);
+    };
+    const int32_t most = iters(std::min(longest, split));   // spans are at most the split
+    std::fill_n(whole.begin(), most + 1, 0);
+    std::fill_n(split_items.begin(), most + 1, 0);
+    for (const RowLoad& r : rows) {
+      const int32_t span = row_span(r.ctx, split);
+      for (int32_t j = 0; j < r.q; ++j) {
+        const int32_t keys = r.ctx - r.q + j + 1;
+        const int32_t full = keys / span, rest = keys % span;
+        auto& to = full + (rest > 0) > 1 ? split_items : whole;
+        if (full) to[iters(span)] += static_cast<int64_t>(full) * hkv;
+        if (rest) to[iters(rest)] += hkv;
+      }
+    }
+    d = tiles;
+    for (int32_t i = 1; i <= most; ++i) {
+      if (whole[i]) d.emplace_back(kRowFixed + i * block_ns, whole[i]);
+      if (split_items[i]) d.emplace_back(kRowFixed + kRowSplit + i * block_ns, split_items[i]);
+    }
+    const double ns = std::max(list_schedule(d, slots, heap), static_cast<double>(bytes) / rate + kRowFixed) +
+                      kPerItem * static_cast<double>(n);
+    if (best_ns < 0 || ns <= best_ns) {          // ties: the longer span
+      best_ns = ns;
+      best = split;
+    }
+  };
+  bool priced_before = false;
+  for (const int32_t split : kSplits) {
+    if (!priced_before && split >= before) {
+      priced_before = true;
+      if (split != before) price(before);
+    }
+    price(split);
+    if (split >= longest) break;                 // nothing splits from here on
+  }
+  return best;
+}
+
 }  // namespace
 }  // namespace aug
 
@@ -259,7 +433,8 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
   const int32_t kv_elem = s->kv_dtype == AUG_F32 ? 4 : s->kv_dtype == AUG_BF16 ? 2 : 1;
   const bool stream = total_row_keys * s->head_dim * kv_elem * 2 >= kStreamBytes;
   // a launch without tiles runs MFMA row items on eight-wave workgroups
-  const int32_t split = choose_split(total_row_keys, kv_split_tokens, !any_tiled && row_path == AUG_ROWS_MFMA, !any_tiled);
+  const bool wide_rows = !any_tiled && row_path == AUG_ROWS_MFMA;
+  const int32_t split = choose_split(total_row_keys, kv_split_tokens, wide_rows, !any_tiled);
   const int32_t pos_per_tile = kTileRows / g;
   const int32_t kv_bytes_all = s->kv_dtype == AUG_F32 ? 4 : s->kv_dtype == AUG_BF16 ? 2 : 1;
 
@@ -317,6 +492,32 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
     }
   }
 
+  int32_t row_split = split;   // what the row items are cut by
+  if (kv_split_tokens <= 0) {
+    std::vector<RowLoad> rows;
+    std::vector<int64_t> steps(kTileSpanMax / kKeyTile + 1);
+    int64_t tile_partials = 0;
+    for (int32_t r = 0; r < n; ++r) {
+      const int32_t q = b->q_start[r + 1] - b->q_start[r];
+      const int32_t ctx = b->ctx_len[r];
+      if (q == 1 || !tiles_supported(*s)) {
+        rows.push_back({q, ctx});
+        continue;
+      }
+      for (int32_t j0 = 0; j0 < q; j0 += pos_per_tile) {
+        const int32_t nr = std::min(pos_per_tile, q - j0);
+        const TileSpans ts = tile_spans(ctx - q + j0 + nr, tile_span);
+        steps[ts.span / kKeyTile] += static_cast<int64_t>(ts.count) * hkv;
+        if (ts.count > 1) tile_partials += static_cast<int64_t>(nr) * ts.count * hkv;
+      }
+    }
+    Durations tile_items;
+    for (size_t i = 1; i < steps.size(); ++i)
+      if (steps[i]) tile_items.emplace_back(kTileFixed + static_cast<double>(i) * tile_step_ns(*s), steps[i]);
+    row_split = balance_split(*s, rows, tile_items, total_row_keys, split, row_path == AUG_ROWS_MFMA, wide_rows,
+                              !any_tiled, tile_partials);
+  }
+
   // Row items: a request's spans are equal (within one block), so ordering
   // requests by span length orders their items longest first.
   struct RowReq {
@@ -339,10 +540,7 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
         const int32_t key_end = pos0 + nr;
         // long tiles are split into near-equal spans of whole key tiles; each
         // row of a split tile then has one partial per span, stored together
-        const int32_t nsplit = (key_end + tile_span - 1) / tile_span;
-        int32_t span = (key_end + nsplit - 1) / nsplit;
-        span = ((span + kKeyTile - 1) / kKeyTile) * kKeyTile;
-        const int32_t nsp = (key_end + span - 1) / span;
+        const auto [span, nsp] = tile_spans(key_end, tile_span);
         static_assert(kTileSpanMax % kKeyTile == 0 && kTileSpanMin % kKeyTile == 0,
                       "tile spans are whole key tiles");
         // span <= tile_span <= kTileSpanMax, so the kernel's per-item block-id buffer suffices
@@ -377,9 +575,7 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
     }
     // decodes have one row; rows of an untiled prefill get spans of their own length
     const int32_t keys = ctx;  // the longest row of the request
-    const int32_t nspan = (keys + split - 1) / split;
-    int32_t span = (keys + nspan - 1) / nspan;
-    span = ((span + kBlock - 1) / kBlock) * kBlock;
+    const int32_t span = row_span(keys, row_split);
     row_reqs.push_back({r, span, (keys + span - 1) / span, row_item_ns(span, s->head_dim, kv_bytes)});
     for (int32_t j = 0; j < q; ++j) {
       const int32_t k = ctx - q + j + 1;

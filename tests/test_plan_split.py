@@ -1,0 +1,67 @@
+"""The planner's own split of row items: every key of every row is read by
+exactly one span of each KV head whatever split the launch estimate picks, the
+partial slots are distinct, equal batches give equal images, and a batch that
+fitted the library's scratch array under the split by size still does."""
+
+import numpy as np
+import pytest
+
+import paper_2512_04013_amd as aug
+
+SHAPES = [(4, 4, 64, "f32"), (8, 2, 128, "f32"), (16, 8, 64, "bf16"), (32, 8, 128, "bf16"), (64, 8, 128, "bf16"),
+          (32, 8, 128, "fp8"), (64, 8, 128, "fp8")]
+
+
+def _plan(shape, q_len, ctx, **kw):
+    q_start = np.concatenate([[0], np.cumsum(q_len)])
+    bt = np.concatenate([[0], np.cumsum([-(-c // 16) for c in ctx])])
+    info, plan = aug.aug_attn_plan(shape, q_start, ctx, bt, int(bt[-1]), **kw)
+    return info, plan, q_start
+
+
+@pytest.mark.parametrize("seed", range(21))
+def test_spans_partition_every_row(seed):
+    rng = np.random.default_rng(seed)
+    hq, hkv, d, kv = SHAPES[seed % len(SHAPES)]
+    qd = "f32" if kv == "f32" else "bf16"
+    shape = aug.make_shape(hq, hkv, d, qd, kv, qd, 0.1)
+    n = int(rng.choice([1, 2, 5, 17, 60, 300]))
+    ctx = np.clip(np.exp(rng.uniform(0, np.log(12000), n)), 1, None).astype(int)
+    q_len = np.where(rng.random(n) < 0.2, np.minimum(ctx, rng.integers(1, 40, n)), 1)
+    info, plan, q_start = _plan(shape, q_len, ctx)
+    again = _plan(shape, q_len, ctx)[1]
+    assert np.array_equal(plan, again)
+    raw = plan[64:64 + 48 * info.num_items].reshape(-1, 48)
+    i32, i16 = raw.view(np.int32).reshape(-1, 12), raw.view(np.int16).reshape(-1, 24)
+    row = raw[:, 2] == 0
+    parts = i32[row, 7]
+    assert len(set(parts[parts >= 0])) == (parts >= 0).sum()
+    spans = {}
+    for item, kvh in zip(i32[row], i16[row, 0]):
+        spans.setdefault((int(item[1]), int(kvh)), []).append((int(item[3]), int(item[4])))
+    for r in range(n):
+        if q_len[r] > 1 and kv != "f32":
+            continue                                     # tiles
+        for j in range(q_len[r]):
+            for h in range(hkv):
+                got = sorted(spans.pop((int(q_start[r]) + j, h)))
+                ends = [e for _, e in got]
+                assert got[0][0] == 0 and ends[-1] == ctx[r] - q_len[r] + j + 1
+                assert [b for b, _ in got[1:]] == ends[:-1] and all(b % 16 == 0 and b < e for b, e in got)
+    assert not spans
+
+
+def test_scratch_limit_is_kept():
+    """Prefill tiles whose partials alone nearly fill the library's scratch
+    array: the row items beside them take no split that would exceed it."""
+    shape = aug.make_shape(64, 8, 128, "bf16", "fp8", "bf16", 0.1)
+    seen = 0
+    for chunks in range(1, 24):
+        for rows in (16, 40, 100):
+            q_len, ctx = [rows] * chunks + [1] * 6, [9000] * chunks + [20000] * 6
+            info, _, _ = _plan(shape, q_len, ctx)
+            nominal, _, _ = _plan(shape, q_len, ctx, kv_split_tokens=info.kv_split_tokens)
+            if nominal.workspace_bytes <= aug.NOALLOC_SCRATCH_BYTES:
+                assert info.workspace_bytes <= aug.NOALLOC_SCRATCH_BYTES
+                seen += info.workspace_bytes > aug.NOALLOC_SCRATCH_BYTES // 2
+    assert seen
