@@ -81,6 +81,9 @@ class MixedAttention:
         rows = int(self.info.total_rows)
         out_dtype = torch.float32 if shape.out_dtype == 0 else torch.bfloat16
         self.out = torch.empty((rows, shape.num_q_heads, shape.head_dim), dtype=out_dtype, device=device)
+        # what append() asks of the new K/V rows
+        self._new_shape = (rows, shape.num_kv_heads, shape.head_dim)
+        self._new_dtype = torch.float32 if shape.kv_dtype == 0 else torch.bfloat16
 
     def run(self, q: torch.Tensor, stream=None, kv: "PagedKV" = None, block_ids: torch.Tensor = None,
             out: torch.Tensor = None):
@@ -99,10 +102,9 @@ class MixedAttention:
         """Write the batch's new K/V rows ([rows][H_kv][D]) into the pool
         (``kv`` and ``block_ids`` as for ``run``)."""
         kv = self.kv if kv is None else kv
-        want = (int(self.info.total_rows), self.shape.num_kv_heads, self.shape.head_dim)
-        dtype = torch.float32 if self.shape.kv_dtype == 0 else torch.bfloat16
+        want, dtype = self._new_shape, self._new_dtype
         for t in (k_new, v_new):
-            if tuple(t.shape) != want or t.dtype != dtype or not t.is_contiguous():
+            if t.shape != want or t.dtype != dtype or not t.is_contiguous():
                 raise ValueError(f"new K/V rows must be contiguous {dtype} of shape {want}, got "
                                  f"{t.dtype} {tuple(t.shape)}")
         aug_kv_append(self.shape, self.info, self.plan_dev, k_new, v_new, kv.k_cache,
