@@ -342,8 +342,10 @@ size_t aug_kv_record_bytes(const aug_attn_shape* shape);
  * the records of block_ids_dev[0..n_blocks-1] in that order. Data moves
  * through `staging` (device, >= one record; larger staging means fewer,
  * larger copies): a gather kernel fills it, then an asynchronous copy drains
- * it to host_dst, chunk after chunk, all on `stream`. host_dst is complete
- * once the stream reaches the end of this call's work.
+ * it to host_dst, chunk after chunk, all on `stream`. Small images (a few MiB,
+ * host_dst pinned and 16-byte aligned) go straight to host_dst in one kernel
+ * and leave `staging` alone. host_dst is complete once the stream reaches the
+ * end of this call's work.
  * block_ids_dev: device int32[n_blocks]. block_ids_host: the same ids in
  * host memory (required), range-checked against num_pool_blocks before
  * anything is enqueued, so every record of a successful call is the block's
