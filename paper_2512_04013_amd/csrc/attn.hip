@@ -1059,20 +1059,23 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
 // tile items (bf16 MFMA)
 // ---------------------------------------------------------------------------
 
-template <int D, bool DMA>
+template <int KVT, int D>
 struct TileLds {
   static constexpr int KS = D + 8;    // K row stride (elements): 16-byte aligned, conflict-free reads
-  static constexpr int KS8 = D + 16;  // K row stride (bytes) of fp8 keys kept as codes
   // fp8 values kept as codes, transposed: one row of 64 key bytes per
   // dimension (16 bytes of padding spread a 16-row read over all banks)
   static constexpr int VT8 = 80;
   // V row stride (elements): rows 64 bytes apart modulo the 256-byte bank
   // width, so the transposing reads of four consecutive rows hit distinct banks
   static constexpr int VS = D + 32;
-  // bf16 keys and values come by direct loads, rows of D elements without
-  // padding, K then V (see tile_chunk); fp8 ones through registers, padded
-  static constexpr int ROW = D * 2;                       // bytes of an unpadded row
-  static constexpr int STAGE = DMA ? 128 * ROW : 64 * (KS + VS) * 2;   // bytes of one K + V stage
+  // bf16 keys and values, and fp8 keys of head_dim 128 (kept as codes), come
+  // by direct loads, rows of D elements without padding (see tile_chunk); other
+  // fp8 ones through registers, converted and padded. K, then V.
+  static constexpr bool DMA = KVT != KV_FP8;
+  static constexpr bool K8 = KVT == KV_FP8 && D == 128;
+  static constexpr int ROW = K8 ? D : D * 2;              // bytes of an unpadded row
+  static constexpr int KBYTES = DMA || K8 ? 64 * ROW : 64 * KS * 2;
+  static constexpr int STAGE = KBYTES + (DMA ? 64 * ROW : 64 * VS * 2);   // bytes of one K + V stage
   static constexpr int IDS = aug::kTileSpanMax / kBlock + 8; // block ids of one item's key span
   // fp8, per stage and block of the tile: the K scale times the softmax
   // coefficient, log2 of the V scale, and the V scale's reciprocal
@@ -1080,7 +1083,7 @@ struct TileLds {
   static constexpr int SCALES = 2 * NSC * 4;
   static constexpr int BYTES = 2 * STAGE + IDS * 4 + SCALES;
   static_assert(D * VT8 <= 64 * VS * 2, "transposed fp8 values fit the V region of a stage");
-  static_assert(!DMA || 2 * STAGE <= 65536, "direct loads address a stage with 16 bits");
+  static_assert(!(DMA || K8) || 2 * STAGE <= 65536, "direct loads address a stage with 16 bits");
 };
 
 // Direct loads fill LDS in order (lane l of an instruction writes bytes 16 l ..
@@ -1088,9 +1091,10 @@ struct TileLds {
 // 16-byte chunk c of row r sits at chunk c ^ tile_chunk(r) of its row, and the
 // loads permute which chunk each lane fetches. Sixteen rows at one column (the
 // K operands) and four rows at four neighbouring columns (the transposing V
-// reads) then fall on distinct banks.
-template <int D>
+// reads) then fall on distinct banks; so do sixteen 128-byte rows of key codes.
+template <int D, bool K8>
 __device__ __forceinline__ int tile_chunk(int r) {
+  if constexpr (K8) return (r >> 1) & 7;
   return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
 }
 
@@ -1161,11 +1165,20 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
   using TS = TileStage<KVT>;
   using raw_t = typename TS::raw_t;
   constexpr bool FP8 = KVT == KV_FP8;
-  constexpr bool DMA = !FP8;          // bf16 K/V go straight to LDS
-  using L = TileLds<D, DMA>;
-  constexpr bool QK8 = F8 >= 1;
+  using L = TileLds<KVT, D>;
+  constexpr bool DMA = L::DMA;        // bf16 K/V go straight to LDS
+  // Score products of fp8 keys at head_dim 128 run on the fp8 MFMAs, whose rate
+  // is twice bf16's: with the query rounded to one code (QR, by request), or as
+  // the sum of two codes that holds a bf16 query (below). Two products cost
+  // what one bf16 product does, and the keys stay codes: no conversion, half
+  // of the K traffic through LDS, half of the K operand registers. The loop is
+  // not bound by MFMA issue, so that is what counts: 16 chunks of 512 rows,
+  // 64/8 heads, 467 -> 447 us with their append. Head_dim 64 keeps bf16 keys.
+  constexpr bool QK8 = L::K8;
+  constexpr bool QR = F8 >= 1;
   constexpr bool PV8 = F8 >= 2;
-  static_assert(!QK8 || (FP8 && D == 128), "fp8 score products need fp8 keys and head_dim 128");
+  constexpr int QN = QR ? 1 : 2;      // codes per query element
+  static_assert(!QR || QK8, "fp8 score products need fp8 keys and head_dim 128");
   // fp8 probabilities: a lane's P values are stored as E4M3 codes of
   // p * (vs_b / vref) * 2^kPv8Log2, with vs_b the block's V scale and vref the
   // largest V scale of the item; p stays below 2^kSlack between rescales, so
@@ -1195,12 +1208,18 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
   // (and +8) of a 16-key step at dimension m of a 32-dim block
   const int v_lane_off = (4 * hh + (lane & 15) / 4) * L::VS + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
-  // bf16 scores: Q^T operands of the KSTEPS k-steps, dims 16s + 8hh .. + 7.
-  // fp8 scores: the row rounded to E4M3 after division by its scale qscale
-  // (largest magnitude / 448), as the B operands of the two 64-dim k-steps:
-  // lane half hh holds dims 64h + 32hh .. + 31 of k-step h.
+  // bf16 keys: Q^T operands of the KSTEPS k-steps, dims 16s + 8hh .. + 7.
+  // fp8 keys: E4M3 codes of the row after division by its scale qscale, as the
+  // B operands of the two 64-dim k-steps: lane half hh holds dims
+  // 64h + 32hh .. + 31 of k-step h. QR rounds to one code (qscale the largest
+  // magnitude / 448). Otherwise qscale is the power of two that takes the
+  // largest magnitude to [128, 256), q8[0] the rounded row and q8[1] 2^5 times
+  // what the rounding left: at most 8 units of an 8-bit significand, so four
+  // bits hold it. The sum is the bf16 element itself down to 2^-14 of the
+  // largest magnitude, and within 2^-22 of that magnitude below.
+  constexpr int kLoLog2 = 5;
   uint4 qreg[QK8 ? 1 : KSTEPS];
-  v8i_t q8[2];
+  v8i_t q8[QN][2];
   float qscale = 1.f;
   {
     const int64_t qoff = (static_cast<int64_t>(it.q_row0 + p) * a.hq + static_cast<int64_t>(kvh) * G + gh) * D;
@@ -1227,27 +1246,44 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
             amax = fmaxf(amax, fmaxf(fabsf(__uint_as_float(w[e] << 16)), fabsf(__uint_as_float(w[e] & 0xFFFF0000u))));
         }
       amax = max_across_halves(amax);
-      // a vector below 2^-100 (all zero, in practice) rounds to zero: its
-      // reciprocal scale would overflow
-      const bool tiny = !(amax >= 0x1p-100f);
-      qscale = tiny ? 1.f : amax * (1.f / 448.f);
-      const float inv = tiny ? 0.f : 448.f / amax;
+      float inv;
+      if constexpr (QR) {
+        // a vector below 2^-100 (all zero, in practice) rounds to zero: its
+        // reciprocal scale would overflow
+        const bool tiny = !(amax >= 0x1p-100f);
+        qscale = tiny ? 1.f : amax * (1.f / 448.f);
+        inv = tiny ? 0.f : 448.f / amax;
+      } else {
+        // biased exponents 15 .. 254 keep both powers of two normal; a smaller
+        // row (scores below 2^-100) is only shifted less
+        const uint32_t ex = max(__float_as_uint(amax) >> 23, 15u);
+        qscale = __uint_as_float((ex - 7) << 23);
+        inv = __uint_as_float((261u - ex) << 23);
+      }
+      // four dims (two packed words) -> a dword of codes, dim order kept
+      auto codes = [](float x0, float x1, float x2, float x3) {
+        const int w = __builtin_amdgcn_cvt_pk_fp8_f32(x0, x1, 0, false);
+        return __builtin_amdgcn_cvt_pk_fp8_f32(x2, x3, w, true);
+      };
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int c4 = 0; c4 < 4; ++c4) {
           const uint32_t w[4] = {raw[h][c4].x, raw[h][c4].y, raw[h][c4].z, raw[h][c4].w};
-          // eight dims -> two dwords of four E4M3 codes (dim order kept)
-          int lo = __builtin_amdgcn_cvt_pk_fp8_f32(__uint_as_float(w[0] << 16) * inv,
-                                                  __uint_as_float(w[0] & 0xFFFF0000u) * inv, 0, false);
-          lo = __builtin_amdgcn_cvt_pk_fp8_f32(__uint_as_float(w[1] << 16) * inv,
-                                              __uint_as_float(w[1] & 0xFFFF0000u) * inv, lo, true);
-          int hi = __builtin_amdgcn_cvt_pk_fp8_f32(__uint_as_float(w[2] << 16) * inv,
-                                                  __uint_as_float(w[2] & 0xFFFF0000u) * inv, 0, false);
-          hi = __builtin_amdgcn_cvt_pk_fp8_f32(__uint_as_float(w[3] << 16) * inv,
-                                              __uint_as_float(w[3] & 0xFFFF0000u) * inv, hi, true);
-          q8[h][2 * c4] = lo;
-          q8[h][2 * c4 + 1] = hi;
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            float x[4] = {bf16_lo(w[2 * j]) * inv, bf16_hi(w[2 * j]) * inv, bf16_lo(w[2 * j + 1]) * inv,
+                          bf16_hi(w[2 * j + 1]) * inv};
+            const int hi = codes(x[0], x[1], x[2], x[3]);
+            q8[0][h][2 * c4 + j] = hi;
+            if constexpr (!QR) {
+              const auto r0 = __builtin_amdgcn_cvt_pk_f32_fp8(hi, false);
+              const auto r1 = __builtin_amdgcn_cvt_pk_f32_fp8(hi, true);
+              constexpr float up = 1 << kLoLog2;
+              q8[1][h][2 * c4 + j] =
+                  codes((x[0] - r0[0]) * up, (x[1] - r0[1]) * up, (x[2] - r1[0]) * up, (x[3] - r1[1]) * up);
+            }
+          }
         }
     }
   }
@@ -1340,10 +1376,9 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     constexpr bool FULL = decltype(full_tag)::value;
     const int tok0 = k0 + tk * KPT;
     const int slot = (tok0 >> 4) - blk_first;
-    if constexpr (PV8) {
-      load_rows(kc, k0, tk, tc, kr, full_tag);
+    if constexpr (QK8) {
       const int vbid = load_rows(vc, k0, tkv, tcv, vr, full_tag);
-      vsc_reg = vbid >= 0 ? a.v_scale[static_cast<int64_t>(vbid) * a.hkv + kvh] : 1.f;
+      if constexpr (PV8) vsc_reg = vbid >= 0 ? a.v_scale[static_cast<int64_t>(vbid) * a.hkv + kvh] : 1.f;
     } else if constexpr (FULL) {
       const int64_t base = ((static_cast<int64_t>(ids[slot]) * a.hkv + kvh) * head_stride +
                             static_cast<int64_t>(tok0 & 15) * D + 8 * tc) * EB;
@@ -1380,15 +1415,10 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
   };
   auto store_tile = [&](int stage) {
     uint16_t* ks = reinterpret_cast<uint16_t*>(smem + stage * L::STAGE);
-    uint16_t* vs = ks + 64 * L::KS;
+    uint16_t* vs = ks + L::KBYTES / 2;
 #pragma unroll
     for (int u = 0; u < KPT; ++u) {
-      if constexpr (QK8) {
-        // keys stay fp8: rows of KS8 bytes
-        *reinterpret_cast<raw_t*>(reinterpret_cast<unsigned char*>(ks) + (tk * KPT + u) * L::KS8 + 8 * tc) = kr[u];
-      } else {
-        *reinterpret_cast<uint4*>(ks + (tk * KPT + u) * L::KS + 8 * tc) = TS::to_bf16(kr[u]);
-      }
+      if constexpr (!QK8) *reinterpret_cast<uint4*>(ks + (tk * KPT + u) * L::KS + 8 * tc) = TS::to_bf16(kr[u]);
       if constexpr (!PV8) *reinterpret_cast<uint4*>(vs + (tk * KPT + u) * L::VS + 8 * tc) = TS::to_bf16(vr[u]);
     }
     if constexpr (PV8) {
@@ -1433,13 +1463,16 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     }
   };
 
-  // direct loads: wave w fetches block w of a key tile, RPI rows an instruction
+  // direct loads (fp8: of the keys only): wave w fetches block w of a key tile,
+  // RPI rows an instruction
   constexpr int RPI = 1024 / L::ROW;
   const int dma_wave = __builtin_amdgcn_readfirstlane(wave);
   const int dma_row = lane * 16 / L::ROW;            // row within an instruction
-  const uint32_t dma_off = dma_row * L::ROW + (((lane & (L::ROW / 16 - 1)) ^ tile_chunk<D>(dma_row)) << 4);
+  const uint32_t dma_off = dma_row * L::ROW + (((lane & (L::ROW / 16 - 1)) ^ tile_chunk<D, QK8>(dma_row)) << 4);
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
       (__attribute__((address_space(3))) unsigned char*)(smem)));
+  // pools that are not 16-byte aligned (a caller's own offsets) go through registers
+  const bool odd_pool = ((reinterpret_cast<uintptr_t>(kc) | (DMA ? reinterpret_cast<uintptr_t>(vc) : 0)) & 15) != 0;
   int dma_bid = -1;                                   // the block in flight, -1 if none was loaded
   auto issue_tile = [&](int t, int stage) {
     const int tok0 = t * 64 + 16 * dma_wave;
@@ -1448,12 +1481,30 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     if (dma_bid < 0) return;
     const int64_t base = (static_cast<int64_t>(bid) * a.hkv + kvh) * head_stride * EB;
     const uint32_t dst = lds0 + stage * L::STAGE + dma_wave * 16 * L::ROW;
+    if (odd_pool) {
+      // opaque, or the loop's addresses are kept in registers throughout the item
+      uint32_t from = dma_off, to = lane * 16;
+      asm volatile("" : "+v"(from), "+v"(to));
+      unsigned char* block = smem + stage * L::STAGE + dma_wave * 16 * L::ROW;
+#pragma unroll 1
+      for (int i = 0; i < 16 / RPI; ++i) {
+        const uint32_t off = i * 1024 + (from ^ (tile_chunk<D, QK8>(RPI * i) << 4));
+        uint4 x;
+        __builtin_memcpy(&x, kc + base + off, 16);
+        *reinterpret_cast<uint4*>(block + i * 1024 + to) = x;
+        if constexpr (DMA) {
+          __builtin_memcpy(&x, vc + base + off, 16);
+          *reinterpret_cast<uint4*>(block + L::KBYTES + i * 1024 + to) = x;
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < 16 / RPI; ++i) {
       // rows RPI i ..: the chunk permutation of row dma_row, with i's own bits
-      const uint32_t off = i * 1024 + (dma_off ^ (tile_chunk<D>(RPI * i) << 4));
+      const uint32_t off = i * 1024 + (dma_off ^ (tile_chunk<D, QK8>(RPI * i) << 4));
       load_to_lds16(kc + base, off, dst + i * 1024);
-      load_to_lds16(vc + base, off, dst + 64 * L::ROW + i * 1024);
+      if constexpr (DMA) load_to_lds16(vc + base, off, dst + L::KBYTES + i * 1024);
     }
   };
   // This wave's part of tile t is complete: its loads have landed, and rows
@@ -1468,28 +1519,27 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
       for (int i = 0; i < 16 / RPI; ++i)
         if (RPI * i + dma_row >= first) {
           *reinterpret_cast<uint4*>(dst + i * 1024 + lane * 16) = uint4{0, 0, 0, 0};
-          *reinterpret_cast<uint4*>(dst + 64 * L::ROW + i * 1024 + lane * 16) = uint4{0, 0, 0, 0};
+          if constexpr (DMA) *reinterpret_cast<uint4*>(dst + L::KBYTES + i * 1024 + lane * 16) = uint4{0, 0, 0, 0};
         }
     }
   };
-  // operand addresses of the direct layout in a stage: chunk hh of K row n
-  // (rows n and n + 32 share a permutation), and the row and columns of
+  // operand addresses of the direct layout in a stage: chunk hh (codes: 2hh) of
+  // K row n (rows n and n + 32 share a permutation), and the row and columns of
   // v_lane_off in V; the other chunks are exclusive-ors away
-  const uint32_t k_lane = n * L::ROW + ((hh ^ tile_chunk<D>(n)) << 4);
+  const uint32_t k_lane = n * L::ROW + (((QK8 ? 2 * hh : hh) ^ tile_chunk<D, QK8>(n)) << 4);
   const int v_row = 4 * hh + (lane & 15) / 4;
-  const uint32_t v_lane = 64 * L::ROW + v_row * L::ROW +
-                          (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ tile_chunk<D>(v_row)) << 4) + 8 * (lane & 1);
+  const uint32_t v_lane = L::KBYTES + v_row * L::ROW +
+                          (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ tile_chunk<D, QK8>(v_row)) << 4) + 8 * (lane & 1);
 
   auto step = [&](int t, auto mask_tag) {
     constexpr bool MASK = decltype(mask_tag)::value;
     const int k0 = t * 64;
     const int stage = (t - t0) & 1;
-    if constexpr (DMA) settle_tile(t, stage);
+    if constexpr (DMA || QK8) settle_tile(t, stage);
     __syncthreads();   // stage `stage` is written; the other stage's readers are done
     if (t + 1 < t1) {
-      if constexpr (DMA) {
-        issue_tile(t + 1, stage ^ 1);
-      } else {
+      if constexpr (DMA || QK8) issue_tile(t + 1, stage ^ 1);
+      if constexpr (!DMA) {
         store_tile(stage ^ 1);
         if (t + 2 < t1) {
           if (t + 2 < t_full) load_tile(k0 + 128, bool_tag<true>{});
@@ -1499,23 +1549,22 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     }
     const uint32_t k_base = k_lane + stage * L::STAGE, v_base = v_lane + stage * L::STAGE;
     const uint16_t* ks = reinterpret_cast<const uint16_t*>(smem + stage * L::STAGE);
-    const uint16_t* vs = ks + 64 * L::KS;
+    const uint16_t* vs = ks + L::KBYTES / 2;
 
     // S^T = K Q^T for keys k0..k0+63. All K operands of the tile are read
     // from LDS first, so the reads stream while the MFMAs consume them in order.
     f32x16_t sacc[2];
     if constexpr (QK8) {
-      // fp8: K rows of 128 codes against the rounded Q, two 64-dim k-steps
-      // per 32 keys on 32x32x64 fp8 MFMAs (unit block scales)
-      const unsigned char* k8 = reinterpret_cast<const unsigned char*>(ks);
+      // fp8: K rows of 128 codes against the codes of Q, two 64-dim k-steps
+      // per 32 keys on 32x32x64 fp8 MFMAs (block scales 1, and 2^-kLoLog2 for
+      // the queries' second codes, which are added first)
       v8i_t kop[2][2];
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const unsigned char* src = k8 + (32 * mb + n) * L::KS8 + 64 * h + 32 * hh;
-          const uint4 lo = *reinterpret_cast<const uint4*>(src);
-          const uint4 hi = *reinterpret_cast<const uint4*>(src + 16);
+          const uint4 lo = *reinterpret_cast<const uint4*>(smem + (k_base ^ (64 * h)) + 32 * mb * L::ROW);
+          const uint4 hi = *reinterpret_cast<const uint4*>(smem + (k_base ^ (64 * h + 16)) + 32 * mb * L::ROW);
           kop[mb][h] = v8i_t{static_cast<int>(lo.x), static_cast<int>(lo.y), static_cast<int>(lo.z),
                              static_cast<int>(lo.w), static_cast<int>(hi.x), static_cast<int>(hi.y),
                              static_cast<int>(hi.z), static_cast<int>(hi.w)};
@@ -1527,8 +1576,11 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
 #pragma unroll
         for (int e = 0; e < 16; ++e) sacc[mb][e] = 0.f;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-          sacc[mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop[mb][h], q8[h], sacc[mb], 0, 0, 0, 127, 0, 127);
+        for (int i = QN - 1; i >= 0; --i)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            sacc[mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop[mb][h], q8[i][h], sacc[mb], 0, 0, 0, 127, 0,
+                                                                      127 - (i ? kLoLog2 : 0));
       }
     } else {
       uint4 kop[2][KSTEPS];
@@ -1718,9 +1770,8 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
   };
 
   int t = t0;
-  if constexpr (DMA) {
-    issue_tile(t0, 0);
-  } else {
+  if constexpr (DMA || QK8) issue_tile(t0, 0);
+  if constexpr (!DMA) {
     if (t0 < t_full) load_tile(t0 * 64, bool_tag<true>{});
     else load_tile(t0 * 64, bool_tag<false>{});
     store_tile(0);
@@ -1804,7 +1855,7 @@ template <int KVT, int D, int G, int QT, int OT, bool TILES, bool ROW_MFMA, int 
 __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   static_assert(!TILES || NW == kThreads / 64, "tile items run on four-wave workgroups");
   constexpr int RB = row_lds_bytes<D, G, NW>();
-  constexpr int TB = TILES ? TileLds<D, KVT != KV_FP8>::BYTES : 0;
+  constexpr int TB = TILES ? TileLds<KVT, D>::BYTES : 0;
   static_assert(RB >= 4 && (!TILES || TB >= 4), "a split item's workgroup keeps its merge flag in LDS");
   __shared__ __align__(16) unsigned char smem[RB > TB ? RB : TB];
   const WorkItem it = load_item(a.items + blockIdx.x);
