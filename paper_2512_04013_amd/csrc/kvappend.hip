@@ -56,26 +56,49 @@ __device__ __forceinline__ float fp8_value(uint32_t c) {
   return (c & 0x80u) ? -mag : mag;
 }
 
-// float -> E4M3FN code: round to nearest, ties to an even mantissa, every
-// magnitude from 448 up saturates to +-448, the sign of zero is kept.
-__device__ __forceinline__ uint32_t fp8_code(float y) {
-  const uint32_t sign = (__float_as_uint(y) >> 24) & 0x80u;
-  const float a = fabsf(y);
-  uint32_t code;
-  if (!(a < 448.f)) {
-    code = 0x7Eu;
-  } else if (a < 0x1p-6f) {
-    code = static_cast<uint32_t>(__builtin_rintf(a * 512.f));   // subnormal steps of 2^-9 (8 = 2^-6)
-  } else {
-    const uint32_t b = __float_as_uint(a);
-    const uint32_t e = (b >> 23) - 120u;                         // E4M3 exponent field, 1..15
-    const uint32_t m = b & 0x7FFFFFu;
-    const uint32_t rest = m & 0xFFFFFu;
-    uint32_t r = m >> 20;
-    r += (rest > 0x80000u) | ((rest == 0x80000u) & (r & 1u));
-    code = min((e << 3) + r, 0x7Eu);                             // r == 8 carries into the exponent
+// Four floats -> four E4M3FN codes: round to nearest, ties to an even mantissa
+// (the conversion instruction's own rounding, subnormals included); every
+// magnitude from 448 up, and NaN, saturates to +-448; the sign of zero is kept.
+__device__ __forceinline__ uint32_t fp8_codes(const float* y) {
+  float v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = fabsf(y[e]) < 448.f ? y[e] : copysignf(448.f, y[e]);
+  const int w = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], 0, false);
+  return static_cast<uint32_t>(__builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], w, true));
+}
+
+// x / s for many x by one s > 0. `fast` (s within 2^+-60): the correctly rounded
+// reciprocal and two exact remainders give the correctly rounded quotient; a
+// remainder that underflows belongs to a quotient below 2^-40, whose code is 0
+// either way. Otherwise the plain division. Bounded by instructions on large
+// appends: with a division and a code in plain operations per element, 8192
+// rows on the 64/8-head layer took @A0@ us, with these @A1@ (@AB@ MB).
+struct Divide {
+  float s, inv;
+  bool fast;
+  __device__ explicit Divide(float d) : s(d), inv(1.f / d), fast(d >= 0x1p-60f && d <= 0x1p60f) {}
+  __device__ __forceinline__ float operator()(float x) const {
+    if (!fast) return x / s;
+    float q = x * inv;
+    q = fmaf(fmaf(-q, s, x), inv, q);
+    q = fmaf(fmaf(-q, s, x), inv, q);
+    return copysignf(q, x);      // a NaN keeps its sign too
   }
-  return code | sign;
+};
+
+// Largest value over the wave, uniform: rotations within rows of 16 lanes, then
+// one lane of each row.
+template <int CTRL>
+__device__ __forceinline__ float max_with(float v) {
+  const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true);
+  return fmaxf(v, __int_as_float(o));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = max_with<0x121>(max_with<0x122>(max_with<0x124>(max_with<0x128>(v))));   // row_ror
+  float m[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16 * i));
+  return fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
 }
 
 // An append item read with one 16-byte load (the index is the same for the
@@ -154,8 +177,7 @@ __global__ __launch_bounds__(kThreads) void append_fp8_kernel(AppendArgs a) {
     for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(x[p][e]));
   }
   const float s_old = bid_ok && it.slot0 > 0 ? *scale : 0.f;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+  amax = wave_max(amax);
   if (!bid_ok) return;
 
   const float need = amax / 448.f;
@@ -163,36 +185,31 @@ __global__ __launch_bounds__(kThreads) void append_fp8_kernel(AppendArgs a) {
   if (it.slot0 > 0) {
     if (need > s_old) {
       // the scale grows: re-encode the block's earlier tokens
+      const Divide by(need);
       for (int r = r0; r < it.slot0; r += RPP) {
         uint2* q = reinterpret_cast<uint2*>(blk + r * D + col);
         const uint2 c = *q;
-        uint32_t lo = 0, hi = 0;
+        float v[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float v0 = (fp8_value((c.x >> (8 * e)) & 0xFFu) * s_old) / need;
-          const float v1 = (fp8_value((c.y >> (8 * e)) & 0xFFu) * s_old) / need;
-          lo |= fp8_code(v0) << (8 * e);
-          hi |= fp8_code(v1) << (8 * e);
-        }
-        *q = uint2{lo, hi};
+        for (int e = 0; e < 8; ++e) v[e] = by(fp8_value(((e < 4 ? c.x : c.y) >> (8 * (e & 3))) & 0xFFu) * s_old);
+        *q = uint2{fp8_codes(v), fp8_codes(v + 4)};
       }
     } else {
       s = s_old;
     }
   }
+  const Divide by(s);
 #pragma unroll
   for (int p = 0; p < PASSES; ++p) {
     const int r = r0 + p * RPP;
     if (r >= it.n_rows) break;
-    uint32_t lo = 0, hi = 0;
+    uint2 c{0u, 0u};
     if (s != 0.f) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lo |= fp8_code(x[p][e] / s) << (8 * e);
-        hi |= fp8_code(x[p][4 + e] / s) << (8 * e);
-      }
+      for (int e = 0; e < 8; ++e) x[p][e] = by(x[p][e]);
+      c = uint2{fp8_codes(x[p]), fp8_codes(x[p] + 4)};
     }
-    *reinterpret_cast<uint2*>(blk + (it.slot0 + r) * D + col) = uint2{lo, hi};
+    *reinterpret_cast<uint2*>(blk + (it.slot0 + r) * D + col) = c;
   }
   if (lane == 0) *scale = s;
 }
