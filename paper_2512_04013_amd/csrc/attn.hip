@@ -1059,7 +1059,7 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
 // tile items (bf16 MFMA)
 // ---------------------------------------------------------------------------
 
-template <int KVT, int D>
+template <int KVT, int D, int F8>
 struct TileLds {
   static constexpr int KS = D + 8;    // K row stride (elements): 16-byte aligned, conflict-free reads
   // fp8 values kept as codes, transposed: one row of 64 key bytes per
@@ -1068,11 +1068,12 @@ struct TileLds {
   // V row stride (elements): rows 64 bytes apart modulo the 256-byte bank
   // width, so the transposing reads of four consecutive rows hit distinct banks
   static constexpr int VS = D + 32;
-  // bf16 keys and values, and fp8 keys of head_dim 128 (kept as codes), come
-  // by direct loads, rows of D elements without padding (see tile_chunk); other
-  // fp8 ones through registers, converted and padded. K, then V.
+  // bf16 keys and values, and fp8 keys that stay codes (fp8 score products),
+  // come by direct loads, rows of D elements without padding (see tile_chunk);
+  // other fp8 ones through registers, converted and padded. K, then V.
   static constexpr bool DMA = KVT != KV_FP8;
-  static constexpr bool K8 = KVT == KV_FP8 && D == 128;
+  static constexpr bool K8 = F8 >= 1;
+  static_assert(!K8 || (KVT == KV_FP8 && D == 128), "fp8 score products need fp8 keys and head_dim 128");
   static constexpr int ROW = K8 ? D : D * 2;              // bytes of an unpadded row
   static constexpr int KBYTES = DMA || K8 ? 64 * ROW : 64 * KS * 2;
   static constexpr int STAGE = KBYTES + (DMA ? 64 * ROW : 64 * VS * 2);   // bytes of one K + V stage
@@ -1165,20 +1166,15 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
   using TS = TileStage<KVT>;
   using raw_t = typename TS::raw_t;
   constexpr bool FP8 = KVT == KV_FP8;
-  using L = TileLds<KVT, D>;
+  using L = TileLds<KVT, D, F8>;
   constexpr bool DMA = L::DMA;        // bf16 K/V go straight to LDS
-  // Score products of fp8 keys at head_dim 128 run on the fp8 MFMAs, whose rate
-  // is twice bf16's: with the query rounded to one code (QR, by request), or as
-  // the sum of two codes that holds a bf16 query (below). Two products cost
-  // what one bf16 product does, and the keys stay codes: no conversion, half
-  // of the K traffic through LDS, half of the K operand registers. The loop is
-  // not bound by MFMA issue, so that is what counts: 16 chunks of 512 rows,
-  // 64/8 heads, 467 -> 447 us with their append. Head_dim 64 keeps bf16 keys.
+  // Without a request the score products over fp8 keys are bf16 too: the keys
+  // are converted exactly and the query keeps every bit that it has. (A query
+  // as the sum of two E4M3 codes, on the fp8 MFMAs at the cost of one bf16
+  // product, saved 4 % on 16 chunks of 512 rows, 64/8 heads, but elements below
+  // 2^-22 of their row's largest magnitude were lost.)
   constexpr bool QK8 = L::K8;
-  constexpr bool QR = F8 >= 1;
   constexpr bool PV8 = F8 >= 2;
-  constexpr int QN = QR ? 1 : 2;      // codes per query element
-  static_assert(!QR || QK8, "fp8 score products need fp8 keys and head_dim 128");
   // fp8 probabilities: a lane's P values are stored as E4M3 codes of
   // p * (vs_b / vref) * 2^kPv8Log2, with vs_b the block's V scale and vref the
   // largest V scale of the item; p stays below 2^kSlack between rescales, so
@@ -1208,18 +1204,12 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
   // (and +8) of a 16-key step at dimension m of a 32-dim block
   const int v_lane_off = (4 * hh + (lane & 15) / 4) * L::VS + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
-  // bf16 keys: Q^T operands of the KSTEPS k-steps, dims 16s + 8hh .. + 7.
-  // fp8 keys: E4M3 codes of the row after division by its scale qscale, as the
-  // B operands of the two 64-dim k-steps: lane half hh holds dims
-  // 64h + 32hh .. + 31 of k-step h. QR rounds to one code (qscale the largest
-  // magnitude / 448). Otherwise qscale is the power of two that takes the
-  // largest magnitude to [128, 256), q8[0] the rounded row and q8[1] 2^5 times
-  // what the rounding left: at most 8 units of an 8-bit significand, so four
-  // bits hold it. The sum is the bf16 element itself down to 2^-14 of the
-  // largest magnitude, and within 2^-22 of that magnitude below.
-  constexpr int kLoLog2 = 5;
+  // bf16 scores: Q^T operands of the KSTEPS k-steps, dims 16s + 8hh .. + 7.
+  // fp8 scores: the row rounded to E4M3 after division by its scale qscale
+  // (largest magnitude / 448), as the B operands of the two 64-dim k-steps:
+  // lane half hh holds dims 64h + 32hh .. + 31 of k-step h.
   uint4 qreg[QK8 ? 1 : KSTEPS];
-  v8i_t q8[QN][2];
+  v8i_t q8[2];
   float qscale = 1.f;
   {
     const int64_t qoff = (static_cast<int64_t>(it.q_row0 + p) * a.hq + static_cast<int64_t>(kvh) * G + gh) * D;
@@ -1246,20 +1236,11 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
             amax = fmaxf(amax, fmaxf(fabsf(__uint_as_float(w[e] << 16)), fabsf(__uint_as_float(w[e] & 0xFFFF0000u))));
         }
       amax = max_across_halves(amax);
-      float inv;
-      if constexpr (QR) {
-        // a vector below 2^-100 (all zero, in practice) rounds to zero: its
-        // reciprocal scale would overflow
-        const bool tiny = !(amax >= 0x1p-100f);
-        qscale = tiny ? 1.f : amax * (1.f / 448.f);
-        inv = tiny ? 0.f : 448.f / amax;
-      } else {
-        // biased exponents 15 .. 254 keep both powers of two normal; a smaller
-        // row (scores below 2^-100) is only shifted less
-        const uint32_t ex = max(__float_as_uint(amax) >> 23, 15u);
-        qscale = __uint_as_float((ex - 7) << 23);
-        inv = __uint_as_float((261u - ex) << 23);
-      }
+      // a vector below 2^-100 (all zero, in practice) rounds to zero: its
+      // reciprocal scale would overflow
+      const bool tiny = !(amax >= 0x1p-100f);
+      qscale = tiny ? 1.f : amax * (1.f / 448.f);
+      const float inv = tiny ? 0.f : 448.f / amax;
       // four dims (two packed words) -> a dword of codes, dim order kept
       auto codes = [](float x0, float x1, float x2, float x3) {
         const int w = __builtin_amdgcn_cvt_pk_fp8_f32(x0, x1, 0, false);
@@ -1271,19 +1252,9 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
         for (int c4 = 0; c4 < 4; ++c4) {
           const uint32_t w[4] = {raw[h][c4].x, raw[h][c4].y, raw[h][c4].z, raw[h][c4].w};
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            float x[4] = {bf16_lo(w[2 * j]) * inv, bf16_hi(w[2 * j]) * inv, bf16_lo(w[2 * j + 1]) * inv,
-                          bf16_hi(w[2 * j + 1]) * inv};
-            const int hi = codes(x[0], x[1], x[2], x[3]);
-            q8[0][h][2 * c4 + j] = hi;
-            if constexpr (!QR) {
-              const auto r0 = __builtin_amdgcn_cvt_pk_f32_fp8(hi, false);
-              const auto r1 = __builtin_amdgcn_cvt_pk_f32_fp8(hi, true);
-              constexpr float up = 1 << kLoLog2;
-              q8[1][h][2 * c4 + j] =
-                  codes((x[0] - r0[0]) * up, (x[1] - r0[1]) * up, (x[2] - r1[0]) * up, (x[3] - r1[1]) * up);
-            }
-          }
+          for (int j = 0; j < 2; ++j)
+            q8[h][2 * c4 + j] = codes(bf16_lo(w[2 * j]) * inv, bf16_hi(w[2 * j]) * inv, bf16_lo(w[2 * j + 1]) * inv,
+                                      bf16_hi(w[2 * j + 1]) * inv);
         }
     }
   }
@@ -1555,9 +1526,8 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     // from LDS first, so the reads stream while the MFMAs consume them in order.
     f32x16_t sacc[2];
     if constexpr (QK8) {
-      // fp8: K rows of 128 codes against the codes of Q, two 64-dim k-steps
-      // per 32 keys on 32x32x64 fp8 MFMAs (block scales 1, and 2^-kLoLog2 for
-      // the queries' second codes, which are added first)
+      // fp8: K rows of 128 codes against the rounded Q, two 64-dim k-steps
+      // per 32 keys on 32x32x64 fp8 MFMAs (unit block scales)
       v8i_t kop[2][2];
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
@@ -1576,11 +1546,8 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
 #pragma unroll
         for (int e = 0; e < 16; ++e) sacc[mb][e] = 0.f;
 #pragma unroll
-        for (int i = QN - 1; i >= 0; --i)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            sacc[mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop[mb][h], q8[i][h], sacc[mb], 0, 0, 0, 127, 0,
-                                                                      127 - (i ? kLoLog2 : 0));
+        for (int h = 0; h < 2; ++h)
+          sacc[mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop[mb][h], q8[h], sacc[mb], 0, 0, 0, 127, 0, 127);
       }
     } else {
       uint4 kop[2][KSTEPS];
@@ -1855,7 +1822,7 @@ template <int KVT, int D, int G, int QT, int OT, bool TILES, bool ROW_MFMA, int 
 __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   static_assert(!TILES || NW == kThreads / 64, "tile items run on four-wave workgroups");
   constexpr int RB = row_lds_bytes<D, G, NW>();
-  constexpr int TB = TILES ? TileLds<KVT, D>::BYTES : 0;
+  constexpr int TB = TILES ? TileLds<KVT, D, F8>::BYTES : 0;
   static_assert(RB >= 4 && (!TILES || TB >= 4), "a split item's workgroup keeps its merge flag in LDS");
   __shared__ __align__(16) unsigned char smem[RB > TB ? RB : TB];
   const WorkItem it = load_item(a.items + blockIdx.x);

@@ -1,10 +1,7 @@
-"""Prefill tiles whose keys come by direct loads: fp8 keys kept as codes and
-multiplied with a query split into two codes, at the ends of the split's range,
-and pools at an offset that the direct loads do not take.
+"""Prefill tiles over fp8 KV with queries of every magnitude, and pools at an
+offset that the direct loads to LDS do not take.
 
-The split holds a bf16 query element exactly down to 2^-14 of its row's largest
-magnitude and within 2^-22 of that magnitude below, far inside the bf16 gate; a
-query rounded to one code misses the gate on these sharp keys (0.1 of an
+A query rounded to one code misses the bf16 gate on these sharp keys (0.1 of an
 output)."""
 
 import numpy as np
