@@ -171,6 +171,28 @@ double block_latency_ns(const aug_attn_shape& s, bool mfma) {
 }
 double tile_step_ns(const aug_attn_shape& s) { return s.head_dim == 64 ? 1100 : 2000; }
 
+// Whether the decodes' row items load their K/V past the caches: the launch
+// reads enough of it (kStreamBytes) and, where the block table tells, most of
+// it once. Rows of one chunk read the same keys and never stream.
+bool streams_kv(const aug_batch_desc& b, int32_t hkv, int64_t decode_keys, int64_t key_bytes) {
+  if (decode_keys * key_bytes < kStreamBytes) return false;
+  if (!b.block_ids) return true;
+  std::vector<uint64_t> seen((static_cast<size_t>(b.num_pool_blocks) + 63) / 64);
+  int64_t again = 0;    // blocks of requests that share them, beyond the first
+  for (int32_t r = 0; r < b.num_reqs; ++r) {
+    if (b.q_start[r + 1] - b.q_start[r] != 1) continue;
+    const int32_t* ids = b.block_ids + b.bt_start[r];
+    for (int32_t i = 0, n = (b.ctx_len[r] + kBlock - 1) / kBlock; i < n; ++i) {
+      uint64_t& word = seen[static_cast<uint32_t>(ids[i]) >> 6];
+      const uint64_t bit = uint64_t{1} << (ids[i] & 63);
+      again += (word & bit) != 0;
+      word |= bit;
+    }
+  }
+  const int64_t once = decode_keys - again * kBlock * hkv;
+  return once * key_bytes >= kStreamBytes && 2 * once >= decode_keys;
+}
+
 using Durations = std::vector<std::pair<double, int64_t>>;   // (ns, number of items)
 
 // Makespan of the items on `slots` slots, longest first. Slots that are free at
@@ -225,16 +247,19 @@ struct RowLoad {           // rows that become row items
 // Launches with many items keep a rule on sizes (their rounds even out): spans
 // of one slot's share of all keys, up to the same cap.
 int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows, const Durations& tiles,
-                      int64_t total_row_keys, int32_t before, bool mfma, bool wide_rows, bool rows_only,
-                      int64_t tile_partials) {
-  if (rows.empty()) return before;
+                      int64_t total_row_keys, int64_t row_kv_keys, int32_t before, bool mfma, bool wide_rows,
+                      bool rows_only, int64_t tile_partials) {
+  // Chunks without tiles read their keys once per row, out of the caches, which
+  // the prices below do not know (8 fp32 chunks of 16 rows over 2000 keys: 52 us
+  // cut by size, 65 by price).
+  if (rows.empty() || total_row_keys > 2 * row_kv_keys) return before;
   const int32_t hkv = s.num_kv_heads;
   const int32_t g = s.num_q_heads / hkv;
   const int32_t waves = wide_rows ? 8 : 4;
   // bf16 rows in eight waves leave room for one workgroup a CU
   const int64_t slots = wide_rows && s.kv_dtype == AUG_BF16 ? kSlots / 2 : kSlots;
   const int64_t block_bytes = int64_t{2} * kBlock * s.head_dim * (s.kv_dtype == AUG_F32 ? 4 : s.kv_dtype == AUG_BF16 ? 2 : 1);
-  const int64_t bytes = total_row_keys * block_bytes / kBlock;
+  const int64_t row_kv_bytes = row_kv_keys * block_bytes / kBlock;
   int64_t n_tiles = 0;
   for (const auto& t : tiles) n_tiles += t.second;
   int64_t parts = 0;
@@ -263,7 +288,7 @@ int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows,
   const int64_t part_bytes = partial_floats(g, s.head_dim) * 4;
   const int64_t max_parts =
       std::max<int64_t>(parts_before, static_cast<int64_t>(AUG_NOALLOC_SCRATCH_BYTES) / part_bytes - tile_partials - 1);
-  const double rate = bytes >= kStreamBytes ? kMemoryRate : kCachedRate;
+  const double rate = row_kv_bytes >= kStreamBytes ? kMemoryRate : kCachedRate;
   const double latency = block_latency_ns(s, mfma);
   int32_t longest = 0;
   for (const RowLoad& r : rows) longest = std::max(longest, r.ctx);
@@ -298,7 +323,7 @@ int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows,
       if (whole[i]) d.emplace_back(kRowFixed + i * block_ns, whole[i]);
       if (split_items[i]) d.emplace_back(kRowFixed + kRowSplit + i * block_ns, split_items[i]);
     }
-    const double ns = std::max(list_schedule(d, slots, heap), static_cast<double>(bytes) / rate + kRowFixed) +
+    const double ns = std::max(list_schedule(d, slots, heap), static_cast<double>(row_kv_bytes) / rate + kRowFixed) +
                       kPerItem * static_cast<double>(n);
     if (best_ns < 0 || ns <= best_ns) {          // ties: the longer span
       best_ns = ns;
@@ -372,7 +397,9 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
   if (n > 0 && b->q_start[0] != 0) return fail(AUG_ERR_INVALID, "%s: q_start[0] != 0", who);
   const int32_t hkv = s->num_kv_heads;
   const int32_t g = s->num_q_heads / hkv;
-  int64_t total_row_keys = 0;
+  int64_t total_row_keys = 0;   // keys that row items read, per KV head read once for each of a request's rows
+  int64_t row_kv_keys = 0;      // the same, each request's K/V counted once
+  int64_t decode_keys = 0;      // of that, the requests of one row
   bool any_tiled = false;
   for (int32_t r = 0; r < n; ++r) {
     const int64_t q = static_cast<int64_t>(b->q_start[r + 1]) - b->q_start[r];
@@ -402,6 +429,8 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
     if (!tiled) {
       // rows at positions ctx-q .. ctx-1 read pos+1 keys each
       total_row_keys += (q * (2 * ctx - q + 1) / 2) * hkv;
+      row_kv_keys += ctx * hkv;
+      if (q == 1) decode_keys += ctx * hkv;
     }
   }
   const int64_t total_rows = n > 0 ? b->q_start[n] : 0;
@@ -431,7 +460,8 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
   }
 
   const int32_t kv_elem = s->kv_dtype == AUG_F32 ? 4 : s->kv_dtype == AUG_BF16 ? 2 : 1;
-  const bool stream = total_row_keys * s->head_dim * kv_elem * 2 >= kStreamBytes;
+  const int64_t key_bytes = int64_t{2} * s->head_dim * kv_elem;   // K and V of one key and KV head
+  const bool stream = streams_kv(*b, hkv, decode_keys, key_bytes);
   // a launch without tiles runs MFMA row items on eight-wave workgroups
   const bool wide_rows = !any_tiled && row_path == AUG_ROWS_MFMA;
   const int32_t split = choose_split(total_row_keys, kv_split_tokens, wide_rows, !any_tiled);
@@ -514,8 +544,8 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
     Durations tile_items;
     for (size_t i = 1; i < steps.size(); ++i)
       if (steps[i]) tile_items.emplace_back(kTileFixed + static_cast<double>(i) * tile_step_ns(*s), steps[i]);
-    row_split = balance_split(*s, rows, tile_items, total_row_keys, split, row_path == AUG_ROWS_MFMA, wide_rows,
-                              !any_tiled, tile_partials);
+    row_split = balance_split(*s, rows, tile_items, total_row_keys, row_kv_keys, split,
+                              row_path == AUG_ROWS_MFMA, wide_rows, !any_tiled, tile_partials);
   }
 
   // Row items: a request's spans are equal (within one block), so ordering
@@ -689,7 +719,7 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
           WorkItem it{};
           it.kvh = static_cast<int16_t>(h);
           it.kind = kRowItem;
-          it.stream = stream ? 1 : 0;
+          it.stream = stream && q == 1 ? 1 : 0;
           it.q_row0 = b->q_start[r] + j;
           it.n_rows = 1;
           it.part_stride = 1;

@@ -4,7 +4,10 @@ changes no bit of a result."""
 import numpy as np
 import pytest
 
-import paper_2512_04013_amd as aug
+# before the library: both then use torch's HIP runtime
+torch = pytest.importorskip("torch")
+
+import paper_2512_04013_amd as aug  # noqa: E402
 
 HEADER, ITEM = 64, 48
 STREAM_BYTES = 100_000_000
@@ -32,12 +35,47 @@ def test_flag_follows_the_row_bytes(kv, elem):
         assert len(rows) and (rows[:, 3] == want).all() and not items[items[:, 2] == 1][:, 3].any()
 
 
+def test_rows_of_one_chunk_are_not_flagged():
+    """fp32 chunks become row items that read the same keys once per row: over
+    the limit counted so, far under it counted once."""
+    shape = aug.make_shape(8, 2, 128, "f32", "f32", "f32", 0.1)
+    q_len, ctx = [64] * 16, [576] * 16
+    row_bytes = sum(c * (c + 1) // 2 - (c - q) * (c - q + 1) // 2 for q, c in zip(q_len, ctx)) * 2 * 2 * 128 * 4
+    assert sum(ctx) * 2 * 2 * 128 * 4 < STREAM_BYTES // 4 and row_bytes > 4 * STREAM_BYTES
+    bt = np.concatenate([[0], np.cumsum([c // 16 for c in ctx])])
+    info, plan = aug.aug_attn_plan(shape, np.arange(17) * 64, ctx, bt, int(bt[-1]))
+    assert not _items(info, plan)[:, 3].any()
+    # beside decodes that stream, they still do not
+    q_len, ctx = q_len + [1] * 8, ctx + [20000] * 8
+    bt = np.concatenate([[0], np.cumsum([-(-c // 16) for c in ctx])])
+    info, plan = aug.aug_attn_plan(shape, np.concatenate([[0], np.cumsum(q_len)]), ctx, bt, int(bt[-1]))
+    items = _items(info, plan)
+    row0 = np.ascontiguousarray(items[:, 4:8]).view(np.int32)[:, 0]
+    assert (items[row0 < 1024, 3] == 0).all() and (items[row0 >= 1024, 3] == 1).all()
+
+
+@pytest.mark.parametrize("shared,want", [(0, 1), (20, 1), (200, 0)])
+def test_blocks_shared_by_requests_count_once(shared, want):
+    """64 decodes of 220 blocks whose first `shared` blocks are the same pool
+    blocks: 14 MB are read over and over where 200 are shared. Without the
+    block table the planner cannot know."""
+    shape = aug.make_shape(64, 8, 128, "bf16", "fp8", "bf16", 0.1)
+    n, nblk = 64, 220
+    own = nblk - shared
+    ids = np.concatenate([np.concatenate([np.arange(shared), shared + r * own + np.arange(own)]) for r in range(n)])
+    args = shape, np.arange(n + 1), [nblk * 16 - 5] * n, np.arange(n + 1) * nblk, n * nblk
+    info, plan = aug.aug_attn_plan(*args, block_ids=ids)
+    assert (_items(info, plan)[:, 3] == want).all()
+    blind, plan = aug.aug_attn_plan(*args)
+    assert (_items(blind, plan)[:, 3] == 1).all()
+    assert blind.num_items == info.num_items and blind.workspace_bytes == info.workspace_bytes
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,g,kv,row_path", [(64, 1, "f32", 0), (128, 2, "f32", 0), (64, 4, "bf16", 0), (128, 1, "bf16", 0),
                                              (128, 4, "bf16", 1), (128, 4, "bf16", 2), (128, 8, "bf16", 2),
                                              (128, 2, "fp8", 0), (128, 4, "fp8", 2), (128, 8, "fp8", 2)])
 def test_flag_changes_no_bit(d, g, kv, row_path):
-    torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
     from paper_2512_04013_amd import runtime as rt
