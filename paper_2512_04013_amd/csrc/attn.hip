@@ -145,12 +145,10 @@ __device__ __forceinline__ float group_sum(float v) {
 // KV element formats for the row path
 // ---------------------------------------------------------------------------
 
-// Loads of K/V that the launch reads once. STREAM marks them non-temporal, so
-// that they leave the caches to the data that is read again: on launches that
-// read more than the caches hold (plan_format.h, WorkItem::stream) the same
-// loads then run at 6.4 TB/s instead of 5.8 (256 decodes over 418k keys, bf16,
-// 295 -> 268 us). Smaller launches find part of their K/V in the 256 MB
-// last-level cache and lose up to a quarter by it.
+// Loads of K/V that the launch reads once. STREAM marks them non-temporal: they
+// do not allocate in the 256 MB memory-side cache, and HBM then delivers 6.4
+// TB/s instead of 5.8 (256 decodes over 418k keys, bf16, 295 -> 268 us). Which
+// items do so, and what it costs them, stands with kStreamBytes in plan_format.h.
 template <bool STREAM, typename T>
 __device__ __forceinline__ T load_kv(const char* p) {
   typedef uint32_t vec_t __attribute__((ext_vector_type(sizeof(T) / 4)));

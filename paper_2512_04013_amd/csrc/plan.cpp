@@ -172,10 +172,10 @@ double block_latency_ns(const aug_attn_shape& s, bool mfma) {
 double tile_step_ns(const aug_attn_shape& s) { return s.head_dim == 64 ? 1100 : 2000; }
 
 // Whether the decodes' row items load their K/V past the caches: the launch
-// reads enough of it (kStreamBytes) and, where the block table tells, most of
+// reads enough of it (`from` bytes) and, where the block table tells, most of
 // it once. Rows of one chunk read the same keys and never stream.
-bool streams_kv(const aug_batch_desc& b, int32_t hkv, int64_t decode_keys, int64_t key_bytes) {
-  if (decode_keys * key_bytes < kStreamBytes) return false;
+bool streams_kv(const aug_batch_desc& b, int32_t hkv, int64_t decode_keys, int64_t key_bytes, int64_t from) {
+  if (decode_keys * key_bytes < from) return false;
   if (!b.block_ids) return true;
   std::vector<uint64_t> seen((static_cast<size_t>(b.num_pool_blocks) + 63) / 64);
   int64_t again = 0;    // blocks of requests that share them, beyond the first
@@ -190,7 +190,7 @@ bool streams_kv(const aug_batch_desc& b, int32_t hkv, int64_t decode_keys, int64
     }
   }
   const int64_t once = decode_keys - again * kBlock * hkv;
-  return once * key_bytes >= kStreamBytes && 2 * once >= decode_keys;
+  return once * key_bytes >= from && 2 * once >= decode_keys;
 }
 
 using Durations = std::vector<std::pair<double, int64_t>>;   // (ns, number of items)
@@ -461,7 +461,7 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
 
   const int32_t kv_elem = s->kv_dtype == AUG_F32 ? 4 : s->kv_dtype == AUG_BF16 ? 2 : 1;
   const int64_t key_bytes = int64_t{2} * s->head_dim * kv_elem;   // K and V of one key and KV head
-  const bool stream = streams_kv(*b, hkv, decode_keys, key_bytes);
+  const bool stream = streams_kv(*b, hkv, decode_keys, key_bytes, stream_from(s->head_dim));
   // a launch without tiles runs MFMA row items on eight-wave workgroups
   const bool wide_rows = !any_tiled && row_path == AUG_ROWS_MFMA;
   const int32_t split = choose_split(total_row_keys, kv_split_tokens, wide_rows, !any_tiled);
@@ -699,6 +699,8 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
   auto emit_tiles_longer_than = [&](double ns) {
     while (ti < tiles.size() && tiles[ti].weight >= ns) items[k++] = tiles[ti++].item;
   };
+  // K/V bytes of decodes that the launch still reads through the caches
+  int64_t ordinary = !stream ? INT64_MAX : decode_keys * key_bytes >= kStreamPrefixFrom ? kStreamPrefix : 0;
   for (const RowReq& rr : row_reqs) {
     emit_tiles_longer_than(rr.ns);
     const int32_t r = rr.r;
@@ -719,7 +721,6 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
           WorkItem it{};
           it.kvh = static_cast<int16_t>(h);
           it.kind = kRowItem;
-          it.stream = stream && q == 1 ? 1 : 0;
           it.q_row0 = b->q_start[r] + j;
           it.n_rows = 1;
           it.part_stride = 1;
@@ -729,6 +730,10 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
           it.bt_off = b->bt_start[r];
           it.part = nspan > 1 ? part0 + sidx : -1;
           it.group = group;
+          if (q == 1) {
+            it.stream = ordinary <= 0 ? 1 : 0;
+            ordinary -= (it.key_end - it.key_begin) * key_bytes;
+          }
           items[k++] = it;
         }
       }

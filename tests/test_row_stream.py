@@ -71,6 +71,35 @@ def test_blocks_shared_by_requests_count_once(shared, want):
     assert blind.num_items == info.num_items and blind.workspace_bytes == info.workspace_bytes
 
 
+@pytest.mark.parametrize("hq,hkv,d,kv,elem", [(32, 8, 128, "bf16", 2), (64, 8, 128, "fp8", 1), (8, 2, 128, "f32", 4),
+                                              (16, 4, 64, "bf16", 2), (4, 4, 64, "f32", 4)])
+@pytest.mark.parametrize("chunks", [0, 2])
+def test_large_launches_start_with_ordinary_loads(hq, hkv, d, kv, elem, chunks):
+    """From 640 MB of decodes' K/V the items that start the launch read 320 MB
+    through the caches and the rest stream; just below, all stream, or at
+    head_dim 64 none."""
+    qd = "f32" if kv == "f32" else "bf16"
+    shape = aug.make_shape(hq, hkv, d, qd, kv, qd, 0.1)
+    per_key = hkv * d * elem * 2
+    for total, prefix in ((640_000_000 // per_key + 1, 320_000_000), (640_000_000 // per_key - 1, 0 if d == 128 else None)):
+        n = 40
+        ctx = [total // n + (r % 7 - 3) * 50 for r in range(n)]
+        ctx[-1] += total - sum(ctx)
+        q_len, ctx = [20] * chunks + [1] * n, [300] * chunks + ctx
+        q_start = np.concatenate([[0], np.cumsum(q_len)])
+        bt = np.concatenate([[0], np.cumsum([-(-c // 16) for c in ctx])])
+        info, plan = aug.aug_attn_plan(shape, q_start, ctx, bt, int(bt[-1]))
+        items = _items(info, plan)
+        i32 = np.ascontiguousarray(items).view(np.int32).reshape(-1, 12)
+        decode = (items[:, 2] == 0) & (i32[:, 1] >= q_start[chunks])
+        keys = (i32[:, 4] - i32[:, 3])[decode]
+        assert keys.sum() == total * hkv and not items[~decode, 3].any()
+        before = (np.cumsum(keys) - keys).astype(np.int64) * d * elem * 2
+        want = np.zeros(len(keys), bool) if prefix is None else before >= prefix
+        assert np.array_equal(items[decode, 3] != 0, want)
+        assert prefix is None or want.any()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,g,kv,row_path", [(64, 1, "f32", 0), (128, 2, "f32", 0), (64, 4, "bf16", 0), (128, 1, "bf16", 0),
                                              (128, 4, "bf16", 1), (128, 4, "bf16", 2), (128, 8, "bf16", 2),
