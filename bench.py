@@ -107,6 +107,14 @@ def append_bytes(b, info) -> float:
     return n + items * (16 + 4)
 
 
+def longest_row_item(plan, info) -> int:
+    """Keys of a plan image's longest row item (``info.kv_split_tokens`` is the
+    split by size, which the planner's own cuts need not follow)."""
+    items = plan[64:64 + 48 * info.num_items].reshape(-1, 48)
+    words = np.ascontiguousarray(items[items[:, 2] == 0]).view(np.int32).reshape(-1, 12)
+    return int((words[:, 4] - words[:, 3]).max(initial=0))
+
+
 def traffic_key(workload_name: str, row_path: int = 0, tile_path: int = 0):
     """Name of a workload's counter record: the workload itself on the
     planner's default paths, ``<workload>@<suffix>`` on an opt-in path (the
@@ -668,8 +676,9 @@ def run_workload(name: str, args, log, full: bool = True, row_path: int = 0, til
     for i in range(args.warmup):
         info = step(i, False)
     torch.cuda.synchronize()
+    longest = longest_row_item(plan_host[(args.warmup - 1) & 1].numpy(), info)
     log(f"plan: {info.num_items} items ({info.num_prefill_items} tiles), {info.num_merge_groups} merge "
-        f"groups, split {info.kv_split_tokens} keys")
+        f"groups, split by size {info.kv_split_tokens} keys, longest row item {longest}")
     t_start = time.perf_counter()
     for i in range(args.steps):
         step(args.warmup + i, True)
@@ -726,7 +735,7 @@ def run_workload(name: str, args, log, full: bool = True, row_path: int = 0, til
         "config": {"workload": b.name, "requests": b.num_reqs, "query_rows": rows,
                    "context_tokens": int(b.ctx_len.sum()), "q_heads": b.num_q_heads,
                    "kv_heads": b.num_kv_heads, "head_dim": b.head_dim, "block_size": 16,
-                   "kv_split_tokens": int(info.kv_split_tokens), "seed": args.seed, "pool_copies": n_copies,
+                   "kv_split_tokens": int(info.kv_split_tokens), "longest_row_item_keys": longest, "seed": args.seed, "pool_copies": n_copies,
                    "row_path": {1: "vector ALU", 2: "MFMA"}[int(info.row_path)],
                    "tile_path": {1: "bf16", 2: "fp8 scores (opt-in)",
                                  3: "fp8 scores and values (opt-in)"}[int(info.tile_path)]},

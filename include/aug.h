@@ -129,10 +129,12 @@ typedef struct {
   int32_t num_merge_groups;  /* split (row, KV head) pairs; the first num_tile_merge_groups
                                 belong to prefill tiles */
   int32_t num_partials;      /* split-K partial results */
-  int32_t kv_split_tokens;   /* the requested split, or the planner's split by size: keys per decode
-                                work item (multiple of block_size). Unless a split was requested,
-                                items of small batches may be cut longer or shorter than it,
-                                where that fills the GPU better */
+  int32_t kv_split_tokens;   /* the requested split (keys per decode work item, rounded up to a
+                                multiple of block_size), or the planner's split by size. Unless a
+                                split was requested, the row items may be cut otherwise: of few
+                                items longer or shorter, where that fills the GPU better, of
+                                many longer (up to one resident workgroup's share of all keys).
+                                Passing it back as a request cuts by it */
   int32_t total_rows;        /* q_start[num_reqs] */
   int32_t num_reqs;
   int32_t num_tile_merge_groups;

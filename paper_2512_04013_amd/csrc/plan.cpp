@@ -243,9 +243,10 @@ struct RowLoad {           // rows that become row items
 };
 
 // The split of the row items when the caller leaves it to the planner. `before`
-// is the split that prefill tiles were cut against and `tiles` their items.
-// Launches with many items keep a rule on sizes (their rounds even out): spans
-// of one slot's share of all keys, up to the same cap.
+// is the split by size that prefill tiles were cut against and `tiles` their
+// items. Launches of many items, whose rounds even out, go by size as well: spans
+// of one resident workgroup's share of all keys (up to choose_split's cap), or
+// `before` where that is longer, as with eight-wave workgroups.
 int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows, const Durations& tiles,
                       int64_t total_row_keys, int64_t row_kv_keys, int32_t before, bool mfma, bool wide_rows,
                       bool rows_only, int64_t tile_partials) {

@@ -65,3 +65,20 @@ def test_scratch_limit_is_kept():
                 assert info.workspace_bytes <= aug.NOALLOC_SCRATCH_BYTES
                 seen += info.workspace_bytes > aug.NOALLOC_SCRATCH_BYTES // 2
     assert seen
+
+
+def test_cut_of_many_items():
+    """A launch of 2048 items and more is cut by the longer of the split by size
+    and one slot's share of all keys; a requested split is taken as given. The
+    benchmark reports the cut, not the split by size."""
+    from bench import longest_row_item
+    shape = aug.make_shape(32, 8, 128, "bf16", "bf16", "bf16", 0.1)
+    rng = np.random.default_rng(0)
+    ctx = np.clip(rng.lognormal(np.log(1400), 0.8, 256), 1, 16384).astype(int)
+    info, plan, _ = _plan(shape, [1] * 256, ctx)
+    share = min(6144, -(-int(ctx.sum()) * 8 // 512))
+    assert info.num_items >= 2048 and share > info.kv_split_tokens
+    longest = longest_row_item(plan, info)
+    assert info.kv_split_tokens < longest <= -(-share // 16) * 16
+    asked, plan, _ = _plan(shape, [1] * 256, ctx, kv_split_tokens=info.kv_split_tokens)
+    assert longest_row_item(plan, asked) <= info.kv_split_tokens == asked.kv_split_tokens
