@@ -28,8 +28,9 @@
 namespace {
 
 constexpr int kThreads = 256;
-// Workgroups per record: a record is 2 KiB to 128 KiB, and a few blocks alone
-// must still keep the host link's long round trips full.
+// Workgroups per record (2 * num_kv_heads * 16 * head_dim elements: 64 KiB for
+// eight KV heads of 128 in bf16): a few blocks alone must still keep the host
+// link's long round trips full.
 constexpr int kSlices = 4;
 
 struct RecordGeom {

@@ -1,7 +1,8 @@
 """Park and resume through staging and the copy engine against the direct
 kernels: the same bytes, for record counts on both sides of the size at which
 the direct path ends, for host buffers the kernels cannot take (not 16-byte
-aligned, or not pinned) and for every KV dtype."""
+aligned, or not pinned) and for every KV dtype. A direct transfer leaves the
+staging buffer alone, so the buffer's bytes tell which path ran."""
 
 import numpy as np
 import pytest
@@ -24,6 +25,13 @@ def _host(kind, nbytes):
     return torch.empty(nbytes, dtype=torch.uint8, pin_memory=True)
 
 
+def _moved_directly(pool, move):
+    pool.staging.fill_(0xA5)
+    move()
+    torch.cuda.synchronize()
+    return bool((pool.staging == 0xA5).all())
+
+
 @pytest.mark.parametrize("kv,hkv,d", [("f32", 1, 64), ("bf16", 1, 64), ("fp8", 1, 128), ("f32", 8, 64), ("bf16", 8, 128), ("fp8", 8, 128)])
 @pytest.mark.parametrize("kind", ["pinned", "misaligned", "pageable"])
 @pytest.mark.parametrize("staging_records", [1, 3, 1000])
@@ -39,11 +47,10 @@ def test_every_path_moves_the_same_bytes(kv, hkv, d, kind, staging_records):
     dst = np.array(sorted(set(range(48)) - used)[:len(src)], np.int32)
     host = _host(kind, len(src) * pool.record_bytes)
     say(f"[park paths] {kv} {kind} staging={staging_records}")
-    pool.park(src, torch.from_numpy(src).cuda(), host)
-    torch.cuda.synchronize()
+    src_dev, dst_dev = torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda()
+    assert _moved_directly(pool, lambda: pool.park(src, src_dev, host)) == (kind == "pinned")
     assert np.array_equal(host.numpy(), kvpark.park(b.k_cache, b.v_cache, b.k_scale, b.v_scale, kv, src))
-    pool.resume(dst, torch.from_numpy(dst).cuda(), host)
-    torch.cuda.synchronize()
+    assert _moved_directly(pool, lambda: pool.resume(dst, dst_dev, host)) == (kind == "pinned")
     for t in (pool.k_cache, pool.v_cache, pool.k_scale, pool.v_scale):
         if t is not None:
             raw = t.contiguous().view(torch.uint8).reshape(48, -1).cpu().numpy()
@@ -64,10 +71,9 @@ def test_around_the_direct_limit(blocks):
     src, dst = ids[:blocks].contiguous(), ids[256:256 + blocks].contiguous()
     host = pool.host_buffer(blocks)
     want_k, want_v = k[src.long()].clone(), v[src.long()].clone()
-    pool.park(src.cpu().numpy(), src, host)
-    torch.cuda.synchronize()
+    src_host, dst_host = src.cpu().numpy(), dst.cpu().numpy()
+    assert _moved_directly(pool, lambda: pool.park(src_host, src, host)) == (blocks <= 128)
     rec = host.view(torch.bfloat16).reshape(blocks, 2, 8, 16, 128)
     assert torch.equal(rec[:, 0], want_k.cpu()) and torch.equal(rec[:, 1], want_v.cpu())
-    pool.resume(dst.cpu().numpy(), dst, host)
-    torch.cuda.synchronize()
+    assert _moved_directly(pool, lambda: pool.resume(dst_host, dst, host)) == (blocks <= 128)
     assert torch.equal(k[dst.long()], want_k) and torch.equal(v[dst.long()], want_v)
