@@ -766,10 +766,9 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
 // up with next to fp8 decoding, so the eight heads go through 16x16 bf16
 // MFMAs instead (heads 8..15 of each MFMA are zero padding). Groups of four
 // heads take the same path with heads 4..15 as padding: over fp8 KV, where the
-// vector ALUs fall behind as well (177 against 150 us for 256 decodes), by
-// default; over bf16 KV, where they keep up and the MFMA form only frees issue
-// slots for the loads, when asked for. Per
-// 16-token block and wave:
+// vector ALUs fall behind as well (191 against 150 us for 256 decodes over 418k
+// keys), by default; over bf16 KV, where they keep up and the MFMA form only
+// frees issue slots for the loads, when asked for. Per 16-token block and wave:
 //   S^T[16 keys][16 heads] = K Q^T with four 16x16x32 MFMAs over head_dim.
 //     Lane l holds token l % 16 and 32 dims of the block's K rows, 16 bytes of
 //     every 64 (the four lane groups g = l / 16 of one load cover whole 64-byte
@@ -783,6 +782,17 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
 //     (m = l % 16) of its four tokens 4g .. 4g + 3 with contiguous loads and
 //     only regroups them into (token, token) pairs per dim.
 // The resulting accumulators give lane l head l % 16 and dims 32g .. 32g + 31.
+//
+// Four heads over fp8 KV use four more columns: lanes of column 4 + h compute
+// head h's scores as well and feed PV what the rounding of its probabilities to
+// bf16 left over, which the end adds up. The vector rows that this replaces keep
+// a maximum per lane group, so with few keys most of their probabilities are
+// exact; with plain bf16 probabilities and one maximum for 16 keys the output was
+// up to 15 % further from float64 (5 keys 1.72e-3 / 1.97e-3 relative, 64 keys
+// 2.10e-3 / 2.19e-3, equal from 100 on), and is 1.66e-3 throughout now, which is
+// the rounding of the bf16 output alone. It costs ten vector instructions a block and no MFMA
+// (256 decodes 148.6 / 149.9 us, 10 decodes over 49k keys
+// 23.5 / 23.7).
 
 // max and sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48
 __device__ __forceinline__ float group4_max(float v) {
@@ -887,13 +897,14 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
   static_assert(G == 8 || G == 4, "one 16-column MFMA holds the group's heads");
   constexpr int D = 128;
   constexpr bool FP8 = KVT == KV_FP8;
+  constexpr bool REST = FP8 && G == 4;   // columns 4 .. 7: the rest of the probabilities
   using KV = MfmaRowKv<KVT>;
   constexpr int EB = KV::EB;
   const int lane = threadIdx.x & 63;
   // wave-uniform, so block ids and scales come through scalar loads instead
   // of queueing behind the K/V loads
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int j = lane & 15;            // query head of the group (G..15: padding)
+  const int j = lane & 15;            // query head of the group (then its rest, or padding)
   const int g = lane >> 4;            // keys 4g .. 4g + 3 of a block
   const int kvh = it.kvh;
 
@@ -901,10 +912,10 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
   uint4 qop[4];
   {
     const uint16_t* qb = static_cast<const uint16_t*>(a.q) +
-                         (static_cast<int64_t>(it.q_row0) * a.hq + static_cast<int64_t>(kvh) * G + (j < G ? j : 0)) * D;
+                         (static_cast<int64_t>(it.q_row0) * a.hq + static_cast<int64_t>(kvh) * G + (j & (G - 1))) * D;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      qop[s] = j < G ? *reinterpret_cast<const uint4*>(qb + KV::k_dim(s, g)) : uint4{0, 0, 0, 0};
+      qop[s] = j < (REST ? 2 * G : G) ? *reinterpret_cast<const uint4*>(qb + KV::k_dim(s, g)) : uint4{0, 0, 0, 0};
   }
   const float sc = a.scale_log2;
   float m_run = kNegBig, l_run = 0.f;
@@ -1008,8 +1019,15 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
       m_run = mn;
     }
     const float bias = vlog - m_run;
-    const uint32_t p01 = pack_bf16(__builtin_amdgcn_exp2f(sv[0] + bias), __builtin_amdgcn_exp2f(sv[1] + bias));
-    const uint32_t p23 = pack_bf16(__builtin_amdgcn_exp2f(sv[2] + bias), __builtin_amdgcn_exp2f(sv[3] + bias));
+    float p[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(sv[r] + bias);
+    uint32_t p01 = pack_bf16(p[0], p[1]), p23 = pack_bf16(p[2], p[3]);
+    if constexpr (REST) {
+      const float rest = j & 4 ? 1.f : 0.f;
+      p01 = pack_bf16(fmaf(-bf16_lo(p01), rest, p[0]), fmaf(-bf16_hi(p01), rest, p[1]));
+      p23 = pack_bf16(fmaf(-bf16_lo(p23), rest, p[2]), fmaf(-bf16_hi(p23), rest, p[3]));
+    }
     // the row sum adds exactly the packed probabilities
     const float bsum = dot2_bf16(p23, kBf16PairOne, dot2_bf16(p01, kBf16PairOne, 0.f));
     l_run = FP8 ? fmaf(bsum, vinv, l_run) : l_run + bsum;
@@ -1038,7 +1056,14 @@ __device__ void row_item_mfma(const WorkItem& it, const AttnArgs& a, float* lds)
 
   // this wave's result for head j: dims 32g + 8r + b from oacc[b][r]
   constexpr int ROW = row_lds_stride(D);
-  const float l_tot = group4_sum(l_run);
+  float l_tot = group4_sum(l_run);
+  if constexpr (REST) {               // row_ror:12: lane j receives lane j + 4
+    l_tot += dpp<0x12C>(l_tot);
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) oacc[b][r] += dpp<0x12C>(oacc[b][r]);
+  }
   if (j < G) {
     float* dst = lds + (wave * G + j) * ROW;
 #pragma unroll

@@ -371,12 +371,12 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
                 "and bf16 or fp8 KV", who);
   // AUTO takes the MFMA rows where the vector ALUs cannot keep up with the KV
   // stream: groups of eight heads, and groups of four over fp8 KV (half the
-  // bytes for the same arithmetic). Vector ALUs against MFMA for the latter:
-  // 256 decodes over 418k keys 177 -> 150 us (floor 141 at the card's read
-  // rate), 10 decodes over 49k keys 31.4 -> 23.2 us, 40 decodes beside two
-  // 100-row chunks 87 -> 61 us. Four heads over bf16 stay on the vector ALUs,
-  // which are at the HBM bound there (294 against 289 us for the same 256
-  // decodes), unless asked for.
+  // bytes for the same arithmetic). Vector ALUs against MFMA for the latter, over
+  // a rotation of pools: 256 decodes over 418k keys 191 -> 150 us (floor 141 at
+  // the card's read rate), 10 decodes over 49k keys 34.6 -> 23.7 us, 40 decodes
+  // beside two 100-row chunks 64 -> 55 us. Four heads over bf16 stay on the
+  // vector ALUs, which are at the HBM bound there (294 against 289 us for the
+  // same 256 decodes), unless asked for.
   if (row_path == AUG_ROWS_AUTO)
     row_path = row_mfma_supported(*s) && (s->num_q_heads == 8 * s->num_kv_heads || s->kv_dtype == AUG_FP8_E4M3FN)
                    ? AUG_ROWS_MFMA : AUG_ROWS_VALU;
