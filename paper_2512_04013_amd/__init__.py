@@ -131,11 +131,11 @@ def lib():
     if _HOST_ONLY_LIB:
         L = _HostOnly(L)
     P = C.c_void_p
-    L.aug_attn_plan.argtypes = [C.POINTER(aug_attn_shape), P, C.c_int32, P,
+    L.aug_attn_plan.argtypes = [C.POINTER(aug_attn_shape), C.POINTER(aug_batch_desc), C.c_int32, P,
                                 C.c_size_t, C.POINTER(aug_attn_plan_info)]
-    L.aug_attn_plan_opts.argtypes = [C.POINTER(aug_attn_shape), P,
+    L.aug_attn_plan_opts.argtypes = [C.POINTER(aug_attn_shape), C.POINTER(aug_batch_desc),
                                      C.POINTER(aug_plan_options), P, C.c_size_t, C.POINTER(aug_attn_plan_info)]
-    L.aug_attn_workspace_size.argtypes = [C.POINTER(aug_attn_shape), P, C.c_int32,
+    L.aug_attn_workspace_size.argtypes = [C.POINTER(aug_attn_shape), C.POINTER(aug_batch_desc), C.c_int32,
                                           C.POINTER(C.c_size_t)]
     L.aug_attn_mixed.argtypes = [C.POINTER(aug_attn_shape), C.POINTER(aug_attn_plan_info), P, P, P, P,
                                  P, P, P, C.c_int32, P, P, C.c_size_t, P]
@@ -271,8 +271,8 @@ def _batch_desc(q_start, ctx_len, bt_start, num_pool_blocks, block_ids=None):
     caller keeps alive for the call)."""
     qs, cl, bs = _i32(q_start), _i32(ctx_len), _i32(bt_start)
     bi = None if block_ids is None else _i32(block_ids)
-    desc = _BatchDesc(len(cl), qs.ctypes.data, cl.ctypes.data, bs.ctypes.data,
-                      None if bi is None else bi.ctypes.data, int(num_pool_blocks))
+    desc = aug_batch_desc.from_buffer(_BatchDesc(len(cl), qs.ctypes.data, cl.ctypes.data, bs.ctypes.data,
+                                                 None if bi is None else bi.ctypes.data, int(num_pool_blocks)))
     return desc, (qs, cl, bs, bi)
 
 

@@ -82,3 +82,22 @@ def test_cut_of_many_items():
     assert info.kv_split_tokens < longest <= -(-share // 16) * 16
     asked, plan, _ = _plan(shape, [1] * 256, ctx, kv_split_tokens=info.kv_split_tokens)
     assert longest_row_item(plan, asked) <= info.kv_split_tokens == asked.kv_split_tokens
+
+
+def test_plain_batch_descriptions_are_taken():
+    """The C calls take a description itself, by reference or by pointer, and
+    refuse anything else in its place."""
+    C, lib = aug.C, aug.lib()
+    shape = aug.make_shape(8, 2, 128, "bf16", "bf16", "bf16", 0.1)
+    arrays = [np.array(a, np.int32) for a in ([0, 1, 2], [40, 700], [0, 3, 47])]
+    desc = aug.aug_batch_desc(2, *(a.ctypes.data_as(C.POINTER(C.c_int32)) for a in arrays), None, 64)
+    want, _ = aug.aug_attn_plan(shape, *arrays, 64)
+    for d in (desc, C.byref(desc), C.pointer(desc)):
+        info, n = aug.aug_attn_plan_info(), C.c_size_t()
+        assert lib.aug_attn_plan(shape, d, 0, None, 0, C.byref(info)) == aug.AUG_OK
+        assert bytes(info) == bytes(want)
+        assert lib.aug_attn_plan_opts(shape, d, aug.aug_plan_options(0, 0, 0), None, 0, C.byref(info)) == aug.AUG_OK
+        assert lib.aug_attn_workspace_size(shape, d, 0, C.byref(n)) == aug.AUG_OK and n.value == want.workspace_bytes
+    for d in (shape, C.byref(shape), C.addressof(desc)):
+        with pytest.raises(C.ArgumentError):
+            lib.aug_attn_plan(shape, d, 0, None, 0, C.byref(aug.aug_attn_plan_info()))
