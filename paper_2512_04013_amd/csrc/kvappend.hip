@@ -71,8 +71,10 @@ __device__ __forceinline__ uint32_t fp8_codes(const float* y) {
 // reciprocal and two exact remainders give the correctly rounded quotient; a
 // remainder that underflows belongs to a quotient below 2^-40, whose code is 0
 // either way. Otherwise the plain division. Bounded by instructions on large
-// appends: with a division and a code in plain operations per element, 8192
-// rows on the 64/8-head layer took @A0@ us, with these @A1@ (@AB@ MB).
+// appends: 8192 rows on the 64/8-head layer, 8 KV heads of 128 (33.6 MB of new
+// rows and 16.8 of codes), took 19.6 us with a division and a code in plain
+// operations per element and the maximum by shuffles, and take 11.75 (4.3 TB/s);
+// 256 decode rows 5.27 / 4.04.
 struct Divide {
   float s, inv;
   bool fast;
