@@ -502,8 +502,8 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
   using elem_t = typename F::raw_t;
 
   const int lane = threadIdx.x & 63;
-  // wave-uniform, so block ids and scales come through scalar loads instead
-  // of queueing behind the K/V loads
+  // uniform over the wave, which the compiler cannot see: block ids (and fp8
+  // scales) are vector loads and count with the K/V loads
   const int wave = threadIdx.x >> 6;
   const int dl = lane % LPT;
   const int tsub = lane / LPT;
@@ -790,9 +790,9 @@ __device__ void row_item(const WorkItem& it, const AttnArgs& a, float* lds) {
 // exact; with plain bf16 probabilities and one maximum for 16 keys the output was
 // up to 15 % further from float64 (5 keys 1.72e-3 / 1.97e-3 relative, 64 keys
 // 2.10e-3 / 2.19e-3, equal from 100 on), and is 1.66e-3 throughout now, which is
-// the rounding of the bf16 output alone. It costs ten vector instructions a block and no MFMA
-// (256 decodes 148.6 / 149.9 us, 10 decodes over 49k keys
-// 23.5 / 23.7).
+// the rounding of the bf16 output alone. It costs ten vector
+// instructions a block and no MFMA (256 decodes 148.6 / 149.9 us, 10 decodes over
+// 49k keys 23.5 / 23.7).
 
 // max and sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48
 __device__ __forceinline__ float group4_max(float v) {
@@ -1128,29 +1128,8 @@ __device__ __forceinline__ int tile_chunk(int r) {
 // LDS read that might alias), its own counts only wait for more than they must.
 __device__ __forceinline__ void load_to_lds16(const char* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds), "v"(off), "s"(base) : "memory");
+               :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
-
-// Staging of one thread's share of a key tile: 16-byte bf16 chunks, or
-// 8-byte fp8 chunks converted (exactly) to bf16 on the way into LDS.
-template <int KVT> struct TileStage;
-template <> struct TileStage<KV_BF16> {
-  using raw_t = uint4;
-  __device__ static uint4 to_bf16(const raw_t& r) { return r; }
-};
-template <> struct TileStage<KV_FP8> {
-  using raw_t = uint2;
-  __device__ static uint4 to_bf16(const raw_t& r) {
-    // OCP E4M3FN codes are exactly representable in bf16
-    uint4 o;
-    o.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.x, 1.0f, false));
-    o.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.x, 1.0f, true));
-    o.z = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.y, 1.0f, false));
-    o.w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.y, 1.0f, true));
-    return o;
-  }
-};
-
 
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef bf16x4_t __attribute__((address_space(3))) lds_bf16x4_t;
@@ -1174,8 +1153,9 @@ __device__ __forceinline__ float sum_across_halves(float v) {
 
 // One tile item: up to 128 query rows (kTileRows / G positions x G heads of
 // one KV head) against keys [key_begin, key_end) of the request. Key tiles of
-// 64 go through two LDS stages: while tile t is multiplied, tile t+1 sits in
-// the other stage and tile t+2 is on its way from HBM into registers.
+// 64 go through two LDS stages. Direct loads bring tile t+1 into the other stage
+// while tile t is multiplied; of fp8 K/V that are converted, tile t+1 sits there
+// by then and tile t+2 is on its way from HBM into registers.
 //
 // Tiles that every row reads in full (all keys at or below the first row's
 // position and inside the span, all block ids inside the pool) take a path
@@ -1186,8 +1166,8 @@ __device__ __forceinline__ float sum_across_halves(float v) {
 // P V on fp8 MFMAs (probabilities rounded to E4M3, values as stored).
 template <int KVT, int D, int G, int OT, int F8>
 __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* smem) {
-  using TS = TileStage<KVT>;
-  using raw_t = typename TS::raw_t;
+  using raw_t = uint2;                // eight codes, converted (exactly) to bf16 on the way into LDS
+  using Codes = RowMath<KV_FP8, AUG_BF16>;
   constexpr bool FP8 = KVT == KV_FP8;
   using L = TileLds<KVT, D, F8>;
   constexpr bool DMA = L::DMA;        // bf16 K/V go straight to LDS
@@ -1346,7 +1326,8 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
   }
   const int t_full = bad && !DMA ? t0 : max(t0, min(t1, min(it.pos0 + 1, key_end) / 64));
 
-  // a thread stages KPT consecutive keys of one block (KPT divides 16)
+  // fp8 through registers (bf16 takes none of this): a thread stages KPT
+  // consecutive keys of one block (KPT divides 16)
   raw_t kr[KPT], vr[KPT];
   float sc_reg = 1.f;   // fp8: thread t < 8 carries scale t of the tile (k0..3, v0..3)
   float vsc_reg = 1.f;  // fp8 values: the V scale of the block this thread stages
@@ -1412,8 +1393,8 @@ __device__ void tile_item(const WorkItem& it, const AttnArgs& a, unsigned char* 
     uint16_t* vs = ks + L::KBYTES / 2;
 #pragma unroll
     for (int u = 0; u < KPT; ++u) {
-      if constexpr (!QK8) *reinterpret_cast<uint4*>(ks + (tk * KPT + u) * L::KS + 8 * tc) = TS::to_bf16(kr[u]);
-      if constexpr (!PV8) *reinterpret_cast<uint4*>(vs + (tk * KPT + u) * L::VS + 8 * tc) = TS::to_bf16(vr[u]);
+      if constexpr (!QK8) *reinterpret_cast<uint4*>(ks + (tk * KPT + u) * L::KS + 8 * tc) = Codes::prep(kr[u]);
+      if constexpr (!PV8) *reinterpret_cast<uint4*>(vs + (tk * KPT + u) * L::VS + 8 * tc) = Codes::prep(vr[u]);
     }
     if constexpr (PV8) {
       // V^T: the thread's four keys 4 tkv + t become byte t of one dword per
