@@ -172,12 +172,12 @@ double block_latency_ns(const aug_attn_shape& s, bool mfma) {
 double tile_step_ns(const aug_attn_shape& s) { return s.head_dim == 64 ? 1100 : 2000; }
 
 // Whether the decodes' row items load their K/V past the caches: the launch
-// reads enough of it (`from` bytes) and, where the block table tells, most of
+// reads enough of it (kStreamBytes) and, where the block table tells, most of
 // it once. Rows of one chunk read the same keys and never stream. Requests share
 // whole prefixes, so one block in kSample tells (plans of 64 decodes over 96k
 // blocks take 71 us, 65 without this look and 133 with one at every block).
-bool streams_kv(const aug_batch_desc& b, int32_t hkv, int64_t decode_keys, int64_t key_bytes, int64_t from) {
-  if (decode_keys * key_bytes < from) return false;
+bool streams_kv(const aug_batch_desc& b, int32_t hkv, int64_t decode_keys, int64_t key_bytes) {
+  if (decode_keys * key_bytes < kStreamBytes) return false;
   if (!b.block_ids) return true;
   std::vector<uint64_t> seen((static_cast<size_t>(b.num_pool_blocks) + 63) / 64);
   constexpr int32_t kSample = 8;
@@ -193,7 +193,7 @@ bool streams_kv(const aug_batch_desc& b, int32_t hkv, int64_t decode_keys, int64
     }
   }
   const int64_t once = decode_keys - again * kSample * kBlock * hkv;
-  return once * key_bytes >= from && 2 * once >= decode_keys;
+  return once * key_bytes >= kStreamBytes && 2 * once >= decode_keys;
 }
 
 using Durations = std::vector<std::pair<double, int64_t>>;   // (ns, number of items)
@@ -465,7 +465,7 @@ extern "C" aug_status aug_attn_plan_opts(const aug_attn_shape* s, const aug_batc
 
   const int32_t kv_elem = s->kv_dtype == AUG_F32 ? 4 : s->kv_dtype == AUG_BF16 ? 2 : 1;
   const int64_t key_bytes = int64_t{2} * s->head_dim * kv_elem;   // K and V of one key and KV head
-  const bool stream = streams_kv(*b, hkv, decode_keys, key_bytes, stream_from(s->head_dim));
+  const bool stream = streams_kv(*b, hkv, decode_keys, key_bytes);
   // a launch without tiles runs MFMA row items on eight-wave workgroups
   const bool wide_rows = !any_tiled && row_path == AUG_ROWS_MFMA;
   const int32_t split = choose_split(total_row_keys, kv_split_tokens, wide_rows, !any_tiled);

@@ -15,11 +15,11 @@ constexpr int32_t kTileSpanMin = 256;       // a tile is never split into spans 
 constexpr int32_t kTileSpanMax = 8192;      // longest key span of one tile item (its block ids fit in LDS)
 // Decodes of a launch that read at least this much K/V load it past the caches.
 // Such loads do not allocate in the 256 MB memory-side cache and come from HBM
-// faster. 64 or 256 decodes, layers of head_dim 128 in bf16, fp8 and fp32, a
-// rotation of pools of 4 GB and more, as the layers of a model are read,
-// ordinary against streamed: 128 MB 26.7 / 24.2 us (bf16, four heads), 27.2 /
-// 25.3 (fp8, eight), 31.2 / 28.7 (fp32); 512 MB 93.3 / 84.8, 97.4 / 89.1, 105.5 /
-// 94.3. They gain down to 16 MB there, but a program that comes back to the same
+// faster. 64 or 256 decodes in bf16, fp8 and fp32, a rotation of pools of 4 GB and
+// more, as the layers of a model are read, ordinary against streamed: 128 MB 26.7
+// / 24.2 us (bf16, four heads of 128), 28.7 / 26.2 (four heads of 64), 27.2 / 25.3
+// (fp8, eight heads), 31.2 / 28.7 (fp32); 512 MB 93.3 / 84.8 (bf16 128), 97.4 /
+// 89.1 (fp8), 105.5 / 94.3 (fp32). They gain down to 16 MB there, but a program that comes back to the same
 // K/V within 256 MB of reads finds it cached with ordinary loads: one pool over
 // and over, 32 MB of fp8 8.1 / 9.7 us, 128 MB 23.2 / 24.2, bf16 23.2 / 22.1.
 constexpr int64_t kStreamBytes = 100'000'000;
@@ -33,10 +33,6 @@ constexpr int64_t kStreamBytes = 100'000'000;
 // / 702. Smaller launches would lose more (512 MB in rotation 97.4 / 89.1 / 92.6).
 constexpr int64_t kStreamPrefix = 320'000'000;
 constexpr int64_t kStreamPrefixFrom = 640'000'000;
-// Head_dim 64 streams only from kStreamPrefixFrom up: below, its shorter loads
-// lose what the cache still holds and gain little in rotation (256 MB, 64
-// decodes of equal contexts: one pool 40.7 / 63.0 us, rotation 62.8 / 64.9).
-constexpr int64_t stream_from(int32_t head_dim) { return head_dim == 64 ? kStreamPrefixFrom : kStreamBytes; }
 constexpr int32_t kMaxContext = 1 << 24;    // longest context of one request the planner accepts
 constexpr int32_t kMaxSplit = 1 << 24;      // largest requested decode split (keys per work item)
 
