@@ -131,9 +131,8 @@ typedef struct {
   int32_t num_partials;      /* split-K partial results */
   int32_t kv_split_tokens;   /* the requested split (keys per decode work item, rounded up to a
                                 multiple of block_size), or the planner's split by size. Unless a
-                                split was requested, the row items may be cut otherwise: of few
-                                items longer or shorter, where that fills the GPU better, of
-                                many longer (up to one resident workgroup's share of all keys).
+                                split was requested, the row items of launches with few of
+                                them may be cut longer or shorter, where that fills the GPU better.
                                 Passing it back as a request cuts by it */
   int32_t total_rows;        /* q_start[num_reqs] */
   int32_t num_reqs;

@@ -148,26 +148,41 @@ int32_t choose_split(int64_t total_row_keys, int32_t requested, bool wide_rows, 
 // is full or nearly empty matters more than any per-key rate: 1000 items of 480
 // keys on 512 slots take two rounds where 500 items of twice the keys take one
 // (18 fp8 decodes of 1700 keys beside a 45-row chunk, 64/8 heads: 37.3 -> 31.1
-// us); short contexts on an idle card want spans down to 128 keys (16 fp32
-// decodes of 400 keys 20.2 -> 10.3 us). So each candidate split is priced by
-// list scheduling, longest item first as the kernel's order has it, of
-//   row items:  kRowFixed + blocks per wave * block time (+ kRowSplit if split)
+// us). And spans cost: what a split item adds (its partial, the counter, the
+// merge's start) takes as long as some blocks, and the merge reads a row's spans
+// one round trip after another (one decode of 8000 keys, 16/4 heads of 64: 10.7
+// us in 16 spans, 17.5 in 63). So each candidate split is priced by list
+// scheduling, longest item first as the kernel's order has it, of
+//   row items:  fixed + blocks per wave * block time (+ split if split)
 //   tile items: kTileFixed + steps * tile step
-// plus kPerItem for every item, and never below the K/V at the memory's rate. A
-// block's time is the path's latency per block or its share of the memory rate.
-// Calibrated on 45 batches (the small and middle sizes of every layer shape)
-// at 16 splits each: the split that this picks is within 4 % of the best one in
-// the mean, where one eighth of total keys per CU, at least 512, was 13 % off.
-constexpr double kRowFixed = 2500, kRowSplit = 1600, kTileFixed = 4500, kPerItem = 4;   // ns
-constexpr double kCachedRate = 9000, kMemoryRate = 6400;                                // bytes per ns
+// plus merge for every span of the longest row where it is split and item for
+// every item, and never below the K/V at the rate. A block's time is the path's
+// latency per block, longer by `shared` where every compute unit holds two
+// workgroups, or its share of the rate.
+struct Prices {            // ns; bytes per ns
+  double fixed, split, item, merge, shared, cached_rate, memory_rate;
+};
+// Launches of rows alone: fitted to 377 batches (18 layer shapes, 1 to 100 equal
+// or lognormal decodes) at up to 14 splits each. The pick is within 1.3 % of the
+// best one in the mean (the split by size 11.7 %) and at worst 10 % over the split
+// by size.
+constexpr Prices kRowsAlone = {400, 3900, 1.4, 350, 0.35, 11000, 11000};
+// Beside tiles, whose kernel leaves the rows fewer wavefronts: fitted to the small
+// and middle mixed batches of every layer shape (with the prices above 64 decodes
+// beside two chunks at head_dim 64 took 31.2 instead of 29.4 us).
+constexpr Prices kBesideTiles = {2500, 1600, 4, 0, 0, 9000, 6400};
+constexpr double kTileFixed = 4500;                                     // ns
 constexpr int32_t kSplits[] = {128, 192, 256, 384, 512, 768, 1024, 1280, 1536, 2048, 3072, 4096, 6144, 8192};
 constexpr int32_t kMaxIters = 8192 / kBlock;
 
-double block_latency_ns(const aug_attn_shape& s, bool mfma) {
-  if (s.head_dim == 64) return s.kv_dtype == AUG_F32 ? 400 : 550;
-  if (s.kv_dtype == AUG_F32) return 1700;
-  if (s.kv_dtype == AUG_BF16) return 950;
-  return mfma ? 630 : 1000;
+double block_latency_ns(const aug_attn_shape& s, bool mfma, bool rows_only) {
+  const bool f32 = s.kv_dtype == AUG_F32, bf16 = s.kv_dtype == AUG_BF16;
+  if (!rows_only) return s.head_dim == 64 ? (f32 ? 400 : 550) : f32 ? 1700 : bf16 ? 950 : mfma ? 630 : 1000;
+  const int32_t g = s.num_q_heads / s.num_kv_heads;
+  if (s.head_dim == 64) return g == 8 ? 1500 : f32 ? 750 : 840;
+  if (f32) return g == 8 ? 16000 : g == 4 ? 3700 : 1100;
+  if (mfma) return bf16 ? 1300 : 1130;
+  return g == 8 ? 2500 : g == 4 ? 1700 : bf16 ? 1000 : 920;
 }
 double tile_step_ns(const aug_attn_shape& s) { return s.head_dim == 64 ? 1100 : 2000; }
 
@@ -247,9 +262,10 @@ struct RowLoad {           // rows that become row items
 
 // The split of the row items when the caller leaves it to the planner. `before`
 // is the split by size that prefill tiles were cut against and `tiles` their
-// items. Launches of many items, whose rounds even out, go by size as well: spans
-// of one resident workgroup's share of all keys (up to choose_split's cap), or
-// `before` where that is longer, as with eight-wave workgroups.
+// items. Launches of many items keep it: their rounds even out (spans of one
+// resident workgroup's share of all keys, twice as long, were no faster with
+// head_dim 128 and up to 14 % slower with 64: 300 decodes over 393k keys, 8/8
+// heads, 132 -> 150 us).
 int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows, const Durations& tiles,
                       int64_t total_row_keys, int64_t row_kv_keys, int32_t before, bool mfma, bool wide_rows,
                       bool rows_only, int64_t tile_partials) {
@@ -283,17 +299,14 @@ int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows,
   const int64_t n_before = count(before);
   const int64_t parts_before = parts;
   constexpr int64_t kManyItems = 4 * kSlots;
-  if (n_before >= kManyItems) {
-    const int64_t cap = wide_rows ? 8192 : rows_only ? 6144 : 4096;
-    const int64_t share = std::min(cap, (total_row_keys + kSlots - 1) / kSlots);
-    return std::max<int32_t>(before, static_cast<int32_t>((share + kBlock - 1) / kBlock * kBlock));
-  }
+  if (n_before >= kManyItems) return before;
   // a batch that fits the library's own scratch array keeps fitting it
   const int64_t part_bytes = partial_floats(g, s.head_dim) * 4;
   const int64_t max_parts =
       std::max<int64_t>(parts_before, static_cast<int64_t>(AUG_NOALLOC_SCRATCH_BYTES) / part_bytes - tile_partials - 1);
-  const double rate = row_kv_bytes >= kStreamBytes ? kMemoryRate : kCachedRate;
-  const double latency = block_latency_ns(s, mfma);
+  const Prices& price_of = rows_only ? kRowsAlone : kBesideTiles;
+  const double rate = row_kv_bytes >= kStreamBytes ? price_of.memory_rate : price_of.cached_rate;
+  const double latency = block_latency_ns(s, mfma, rows_only);
   int32_t longest = 0;
   for (const RowLoad& r : rows) longest = std::max(longest, r.ctx);
 
@@ -305,7 +318,9 @@ int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows,
     const int64_t n = count(split);
     if (n >= kManyItems || parts > max_parts) return;
     const double active = static_cast<double>(std::min<int64_t>(slots, n));
-    const double block_ns = std::max(latency, active * waves * static_cast<double>(block_bytes) / rate);
+    const double shared = std::max(0.0, active / (kSlots / 2) - 1.0);   // compute units with two workgroups
+    const double block_ns =
+        std::max(latency * (1.0 + price_of.shared * shared), active * waves * static_cast<double>(block_bytes) / rate);
     const auto iters = [&](int32_t keys) {
       return std::min<int32_t>(kMaxIters, ((keys + kBlock - 1) / kBlock + waves - 1) / waves);
     };
@@ -324,11 +339,14 @@ int32_t balance_split(const aug_attn_shape& s, const std::vector<RowLoad>& rows,
     }
     d = tiles;
     for (int32_t i = 1; i <= most; ++i) {
-      if (whole[i]) d.emplace_back(kRowFixed + i * block_ns, whole[i]);
-      if (split_items[i]) d.emplace_back(kRowFixed + kRowSplit + i * block_ns, split_items[i]);
+      if (whole[i]) d.emplace_back(price_of.fixed + i * block_ns, whole[i]);
+      if (split_items[i]) d.emplace_back(price_of.fixed + price_of.split + i * block_ns, split_items[i]);
     }
-    const double ns = std::max(list_schedule(d, slots, heap), static_cast<double>(row_kv_bytes) / rate + kRowFixed) +
-                      kPerItem * static_cast<double>(n);
+    const int32_t span = row_span(longest, split);
+    const int32_t spans = (longest + span - 1) / span;
+    const double floor = static_cast<double>(row_kv_bytes) / rate + price_of.fixed;
+    const double ns = std::max(list_schedule(d, slots, heap), floor) + price_of.item * static_cast<double>(n) +
+                      (spans > 1 ? price_of.merge * spans : 0.0);
     if (best_ns < 0 || ns <= best_ns) {          // ties: the longer span
       best_ns = ns;
       best = split;

@@ -68,20 +68,37 @@ def test_scratch_limit_is_kept():
 
 
 def test_cut_of_many_items():
-    """A launch of 2048 items and more is cut by the longer of the split by size
-    and one slot's share of all keys; a requested split is taken as given. The
-    benchmark reports the cut, not the split by size."""
+    """A launch of 2048 items and more keeps the split by size, one of fewer may
+    be cut otherwise, a requested split is taken as given. The benchmark reports
+    the cut."""
     from bench import longest_row_item
     shape = aug.make_shape(32, 8, 128, "bf16", "bf16", "bf16", 0.1)
     rng = np.random.default_rng(0)
     ctx = np.clip(rng.lognormal(np.log(1400), 0.8, 256), 1, 16384).astype(int)
     info, plan, _ = _plan(shape, [1] * 256, ctx)
-    share = min(6144, -(-int(ctx.sum()) * 8 // 512))
-    assert info.num_items >= 2048 and share > info.kv_split_tokens
-    longest = longest_row_item(plan, info)
-    assert info.kv_split_tokens < longest <= -(-share // 16) * 16
-    asked, plan, _ = _plan(shape, [1] * 256, ctx, kv_split_tokens=info.kv_split_tokens)
-    assert longest_row_item(plan, asked) <= info.kv_split_tokens == asked.kv_split_tokens
+    assert info.num_items >= 2048 and longest_row_item(plan, info) <= info.kv_split_tokens
+    few, plan, _ = _plan(shape, [1] * 20, [2000] * 20)
+    assert longest_row_item(plan, few) > few.kv_split_tokens
+    asked, plan, _ = _plan(shape, [1] * 20, [2000] * 20, kv_split_tokens=few.kv_split_tokens)
+    assert longest_row_item(plan, asked) <= asked.kv_split_tokens == few.kv_split_tokens
+
+
+@pytest.mark.parametrize("layer", SHAPES + [(8, 8, 64, "bf16"), (16, 2, 64, "bf16"), (8, 8, 128, "fp8")])
+def test_merges_are_priced(layer):
+    """One decode is not cut into spans whose merge outlasts their streaming
+    (8000 keys: 10.7 us in 16 spans, 17.5 in 63), nor a short one cut at all
+    where a wave reads it in a few blocks (300 keys, eight heads on MFMA)."""
+    hq, hkv, d, kv = layer
+    qd = "f32" if kv == "f32" else "bf16"
+    shape = aug.make_shape(hq, hkv, d, qd, kv, qd, 0.1)
+    slow = kv == "f32" and d == 128 and hq > hkv      # few heads' blocks at a time: more spans pay
+    for ctx, most in ((8000, 48 if slow else 40), (60000, 96)):
+        info, _, _ = _plan(shape, [1], [ctx])
+        assert 4 <= info.num_items // hkv <= most
+    info, _, _ = _plan(shape, [1], [100])
+    assert info.num_items == hkv
+    if hq == 8 * hkv and d == 128:
+        assert _plan(shape, [1], [300])[0].num_items == hkv
 
 
 def test_plain_batch_descriptions_are_taken():
